@@ -482,7 +482,8 @@ int tm_chi(const tm_coeffs* c, int m_use, const double* omega, int nomega, doubl
  * or one per parity of the index (TM_EXTRAP_OSC, bi-constant) -- and z is
  * zero (no overlaps were measured there).  TM_EXTRAP_NONE requires
  * m_total == m_use and equals tm_chi.  m_use >= 4 when extrapolating.
- * Work memory on the device: 64 * m_total * nomega bytes.  Synchronous.
+ * Device memory during the call: the inputs and chi (about 104 * m_total +
+ * 72 * nomega bytes).  Synchronous.
  */
 typedef enum { TM_EXTRAP_NONE = 0, TM_EXTRAP_CONSTANT = 1, TM_EXTRAP_OSC = 2 } tm_extrap;
 int tm_chi_extrapolated(const tm_coeffs* c, int m_use, int m_total, tm_extrap mode, const double* omega,

@@ -16,7 +16,7 @@ namespace tml {
 void launch_kin(const System& s, double* kin, const int* d_mill, int npw, int npw_pad, const double* p, hipStream_t st);
 size_t gemm_partial_elems(int nbatch, int M, int Nn, int K);
 void launch_chi(const double2* alpha, const double* beta, const double2* gamma, const double2* z, int nz, int cap,
-                int M, double n1, const double* omega, int nw, double eta, double2* work, double2* chi, int* status,
+                int M, double n1, const double* omega, int nw, double eta, double2* chi, int* status,
                 hipStream_t st);
 
 static thread_local std::string g_err;
@@ -2221,15 +2221,24 @@ static int chi_rows(const tm_coeffs* c, int m_use, int m_total, tm_extrap mode, 
         };
         // host coefficients, extended past M0: alpha, beta, gamma by their mean over
         // the second half of the computed ones (one mean: constant; one per parity
-        // of the index: osc), z = 0 beyond M0 (no measured overlaps there)
-        std::vector<double2> ha(M), hg(M), hz(nz * (size_t)M, cmk(0.0, 0.0));
-        std::vector<double> hb(M);
+        // of the index: osc), z = 0 beyond M0 (no measured overlaps there).  One
+        // buffer, copied in one piece: alpha, gamma, z rows, beta, omega, and (its
+        // last element, 8 bytes of zero) the status word, ahead of chi on the device
+        const size_t nin = ((size_t)M * (2 + 2 + 2 * nz + 1) + nomega + 1 + 1) / 2 * 2;
+        const size_t nchi = nz * (size_t)nomega;
+        std::vector<double> hin(nin, 0.0), hout(1 + 2 * nchi);
+        double2* ha = reinterpret_cast<double2*>(hin.data());
+        double2* hg = ha + M;
+        double2* hz = hg + M;
+        double* hb = reinterpret_cast<double*>(hz + nz * (size_t)M);
+        double* hw = hb + M;
         for (int j = 0; j < M0; ++j) {
             ha[j] = cmk(c->alpha[2 * j], c->alpha[2 * j + 1]);
             hb[j] = c->beta[j];
             hg[j] = cmk(c->gamma[2 * j], c->gamma[2 * j + 1]);
             for (int l = 0; l < nz; ++l) hz[(size_t)l * M + j] = zsrc(l, j);
         }
+        std::copy(omega, omega + nomega, hw);
         if (M > M0) {
             const int np = mode == TM_EXTRAP_OSC ? 2 : 1;
             double2 ma[2] = {cmk(0, 0), cmk(0, 0)}, mg[2] = {cmk(0, 0), cmk(0, 0)};
@@ -2255,37 +2264,39 @@ static int chi_rows(const tm_coeffs* c, int m_use, int m_total, tm_extrap mode, 
                 hg[j] = mg[p];
             }
         }
-        std::vector<void*> mem;
-        struct G {
-            std::vector<void*>& m;
-            ~G() {
-                for (void* p : m) (void)hipFree(p);
-            }
-        } g{mem};
-        auto al = [&](size_t b) {
-            void* p = nullptr;
-            if (hipMalloc(&p, b) != hipSuccess) throw Error{TM_ENOMEM, "hipMalloc failed in tm_chi"};
-            mem.push_back(p);
-            return p;
-        };
-        double2* da = (double2*)al(M * sizeof(double2));
-        double* db = (double*)al(M * sizeof(double));
-        double2* dg = (double2*)al(M * sizeof(double2));
-        double2* dz = (double2*)al(nz * (size_t)M * sizeof(double2));
-        double* dw = (double*)al(nomega * sizeof(double));
-        double2* work = (double2*)al(4 * (size_t)M * nomega * sizeof(double2));
-        double2* dchi = (double2*)al(nz * (size_t)nomega * sizeof(double2));
-        int* dst = (int*)al(sizeof(int));
-        TM_HIP(hipMemcpy(da, ha.data(), M * sizeof(double2), hipMemcpyHostToDevice));
-        TM_HIP(hipMemcpy(db, hb.data(), M * sizeof(double), hipMemcpyHostToDevice));
-        TM_HIP(hipMemcpy(dg, hg.data(), M * sizeof(double2), hipMemcpyHostToDevice));
-        TM_HIP(hipMemcpy(dz, hz.data(), nz * (size_t)M * sizeof(double2), hipMemcpyHostToDevice));
-        TM_HIP(hipMemcpy(dw, omega, nomega * sizeof(double), hipMemcpyHostToDevice));
-        TM_HIP(hipMemset(dst, 0, sizeof(int)));
-        launch_chi(da, db, dg, dz, nz, M, M, c->n1, dw, nomega, eta, work, dchi, dst, nullptr);
+        // A scaled by a power of two so that its largest entry is about 1 (k_chi
+        // squares its pivots): chi = n1 z A^-1 takes the factor back
+        double big = std::fabs(eta);
+        for (size_t i = 0; i < 4 * (size_t)M; ++i) big = std::max(big, std::fabs(hin[i]));  // alpha, gamma
+        for (int j = 0; j < M; ++j) big = std::max(big, std::fabs(hb[j]));
+        for (int w = 0; w < nomega; ++w) big = std::max(big, std::fabs(hw[w]));
+        int ex = 0;
+        if (std::isfinite(big) && big > 0.0) (void)std::frexp(big, &ex);
+        for (size_t i = 0; i < 4 * (size_t)M; ++i) hin[i] = std::ldexp(hin[i], -ex);
+        for (int j = 0; j < M; ++j) hb[j] = std::ldexp(hb[j], -ex);
+        for (int w = 0; w < nomega; ++w) hw[w] = std::ldexp(hw[w], -ex);
+        struct Mem {
+            double* p = nullptr;
+            ~Mem() { (void)hipFree(p); }
+        } mem;
+        if (hipMalloc((void**)&mem.p, (nin + 2 * nchi) * sizeof(double)) != hipSuccess) {
+            (void)hipGetLastError();
+            mem.p = nullptr;
+            throw Error{TM_ENOMEM, "hipMalloc failed in tm_chi"};
+        }
+        double2* da = reinterpret_cast<double2*>(mem.p);
+        double2* dg = da + M;
+        double2* dz = dg + M;
+        double* db = reinterpret_cast<double*>(dz + nz * (size_t)M);
+        double* dw = db + M;
+        double* dst = mem.p + nin - 1;
+        TM_HIP(hipMemcpy(mem.p, hin.data(), nin * sizeof(double), hipMemcpyHostToDevice));
+        launch_chi(da, db, dg, dz, nz, M, M, std::ldexp(c->n1, -ex), dw, nomega, std::ldexp(eta, -ex),
+                   reinterpret_cast<double2*>(mem.p + nin), reinterpret_cast<int*>(dst), nullptr);
+        TM_HIP(hipMemcpy(hout.data(), dst, hout.size() * sizeof(double), hipMemcpyDeviceToHost));
         int status = 0;
-        TM_HIP(hipMemcpy(&status, dst, sizeof(int), hipMemcpyDeviceToHost));
-        TM_HIP(hipMemcpy(chi, dchi, nz * (size_t)nomega * sizeof(double2), hipMemcpyDeviceToHost));
+        std::memcpy(&status, hout.data(), sizeof(int));
+        std::copy(hout.begin() + 1, hout.end(), chi);
         TM_CHECK(status == 0, TM_EINVAL, "singular tridiagonal system (eta = 0 on a pole?)");
         return TM_OK;
     });
