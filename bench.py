@@ -123,9 +123,11 @@ def kernel_models(inp, info, resident: bool, lanes: int = 1):
     plane_bytes = set_bytes / 2 + fields / 2     # u, u' and the fields, shared by density and apply
     return {
         "k_apply_w": dict(flops=apply_flops, flops_pruned=apply_pruned, bytes=plane_bytes),
+        "k_apply_mx": dict(flops=apply_flops, flops_pruned=apply_pruned, bytes=plane_bytes),
         "k_apply_t": dict(flops=apply_flops, flops_pruned=apply_pruned, bytes=plane_bytes),
         "k_apply_planes": dict(flops=apply_flops, flops_pruned=apply_pruned, bytes=plane_bytes),
         "k_density_w": dict(flops=dens_flops, flops_pruned=dens_pruned, bytes=plane_bytes),
+        "k_density_mx": dict(flops=dens_flops, flops_pruned=dens_pruned, bytes=plane_bytes),
         "k_density_t": dict(flops=dens_flops, flops_pruned=dens_pruned, bytes=plane_bytes),
         "k_density": dict(flops=dens_flops, flops_pruned=dens_pruned, bytes=plane_bytes),
         "k_apply_w32": dict(flops=apply_flops, flops_pruned=apply_pruned, bytes=plane_bytes, fp32=True),

@@ -244,6 +244,8 @@ void build_sphere_map(System& s, SphereMap& m, const std::vector<int>& mill3, in
         int m1 = mill3[3 * g], m2 = mill3[3 * g + 1], m3 = mill3[3 * g + 2];
         TM_CHECK(2 * std::abs(m1) < s.n1 && 2 * std::abs(m2) < s.n2 && 2 * std::abs(m3) < s.n3, TM_EINVAL,
                  "a plane-wave sphere does not fit inside the FFT grid");
+        s.mmax[0] = std::max(s.mmax[0], std::abs(m1));
+        s.mmax[1] = std::max(s.mmax[1], std::abs(m2));
         int i1 = ((m1 % s.n1) + s.n1) % s.n1, i2 = ((m2 % s.n2) + s.n2) % s.n2;
         int pos = i1 * s.n2 + i2;
         TM_CHECK(seen.emplace(mkey(m1, m2, m3), g).second, TM_EINVAL, "duplicate Miller index in a sphere");
@@ -355,7 +357,7 @@ void build_qset(System& s, const tm_system_desc* d, int iq, int npw_pad, QSet& q
     std::vector<int> t_nrows_kq(2 * nk), t_nrows_u(2 * nk);
     std::vector<unsigned long long> t_rmask_kq(2 * nk), t_rmask_u(2 * nk);
     std::vector<int> t_uslot(2 * nk);
-    std::vector<short*> t_colidx(2 * nk);
+    std::vector<short*> t_colidx(2 * nk), t_colidx_u(2 * nk);
     for (int ik = 0; ik < nk; ++ik) {
         KBlock& kb = q.kb[ik];
         const int* r = d->roles + ((size_t)iq * nk + ik) * 4;
@@ -427,13 +429,17 @@ void build_qset(System& s, const tm_system_desc* d, int iq, int npw_pad, QSet& q
             TM_LAUNCH(k_pad_copy, dim3((P + 127) / 128, s.nproj), dim3(128), 0, st, vk, npw, P, s.nproj,
                                kb.vkb);
         }
-        // plane position -> column of the k+q sphere (wave-local plane kernels)
-        std::vector<short> ci((size_t)s.n1 * s.n2, (short)-1);
-        for (int c = 0; c < kb.sph_kq.ncol; ++c) ci[kb.sph_kq.h_col_pos[c]] = (short)c;
-        short* d_ci = dev_upload(s, ci.data(), ci.size());
+        // plane position -> column of a sphere (plane kernels)
+        auto column_index = [&](const SphereMap& m) {
+            std::vector<short> ci((size_t)s.n1 * s.n2, (short)-1);
+            for (int c = 0; c < m.ncol; ++c) ci[m.h_col_pos[c]] = (short)c;
+            return dev_upload(s, ci.data(), ci.size());
+        };
+        short* d_ci = column_index(kb.sph_kq);
         for (int side = 0; side < 2; ++side) {
             int b = side * nk + ik;
             t_colidx[b] = d_ci;
+            t_colidx_u[b] = column_index(kb.sph_u[side]);
             t_colptr_kq[b] = kb.sph_kq.col_ptr;
             t_entg_kq[b] = kb.sph_kq.ent_g;
             t_enti3_kq[b] = kb.sph_kq.ent_i3;
@@ -470,6 +476,7 @@ void build_qset(System& s, const tm_system_desc* d, int iq, int npw_pad, QSet& q
     q.ncol_max = col_stride(q.ncol_max);
     q.d_uslot = dev_upload(s, t_uslot.data(), t_uslot.size());
     q.d_colidx_kq = upload_table(s, t_colidx);
+    q.d_colidx_u = upload_table(s, t_colidx_u);
     q.d_rows_kq = upload_table(s, t_rows_kq);
     q.d_rows_u = upload_table(s, t_rows_u);
     q.d_nrows_kq = dev_upload(s, t_nrows_kq.data(), t_nrows_kq.size());
@@ -1672,6 +1679,17 @@ int tm_system_create(const tm_system_desc* d, tm_system** out) {
         s.qs.resize(d->nq);
         const int npw_pad = system_npw_pad(d);
         for (int iq = 0; iq < d->nq; ++iq) build_qset(s, d, iq, npw_pad, s.qs[iq]);
+        s.mx = mx_supported(s.n2, s.n1, s.mmax[1], s.mmax[0]);  // (their axis 1 is i2)
+        for (int i = 0; i < 2 && s.mx; ++i) {
+            auto both = [&](const std::vector<double2>& t, double2*& d, float2*& f) {
+                std::vector<float2> h(t.size());
+                for (size_t j = 0; j < t.size(); ++j) h[j] = Cx<float2>::from(t[j]);
+                d = dev_upload(s, t.data(), t.size());
+                f = dev_upload(s, h.data(), h.size());
+            };
+            both(mx_constants(ns[i]), s.ctab[i], s.ctabf[i]);
+            both(mx_twists(ns[i]), s.twist[i], s.twistf[i]);
+        }
         TM_HIP(hipDeviceSynchronize());
         *out = ts.release();
         return TM_OK;
@@ -1827,10 +1845,10 @@ int tm_system_footprint(const tm_system_desc* d, tm_memory_info* out) {
                 const double npw = d->npw[r[2]];
                 // occupied partners, projector tables (the point's and the padded copy),
                 // restriction maps, kinetic energies, Miller indices, eigenvalues,
-                // plane-position column index, three sphere maps
+                // plane-position column indices, three sphere maps
                 tables += 2.0 * nb * 2 * P * sizeof(double2) + (double)d->nproj * (P + npw) * sizeof(double2) +
                           (2 * P + npw) * sizeof(int) + P * sizeof(double) + 3 * npw * sizeof(int) +
-                          2.0 * nb * sizeof(double) + NP * sizeof(short) +
+                          2.0 * nb * sizeof(double) + 3 * NP * sizeof(short) +
                           2.0 * (npw + d->npw[r[0]] + d->npw[r[1]] + ncol[r[2]] + ncol[r[0]] + ncol[r[1]] + 3) *
                               sizeof(int);
             }

@@ -126,6 +126,31 @@ __global__ void k_density_reduce(const T2* part, double2* rho, long long N, int 
     rho[idx] = cscale(cmk(sx.x + sgn * sy.x, sx.y + sgn * sy.y), scale);
 }
 
+// The same from partials whose planes are [i2][i1] (the matrix-core kernels'),
+// to [i1][i2]: strips of `rows` rows i2, at most 256 points (or one row), turned
+// in LDS so that both sides go in runs.  blockIdx.z: component and right-hand side.
+__global__ void __launch_bounds__(256) k_density_reduce_t(const double2* part, double2* rho, int n1, int n2, int n3,
+                                                          int rows, int nk, int nchunk, double scale) {
+    __shared__ double2 strip[256];
+    const int comp = blockIdx.z & 3, rhs = blockIdx.z >> 2;
+    const long long N = (long long)n1 * n2 * n3, off = (long long)blockIdx.y * n1 * n2;
+    const int r0 = blockIdx.x * rows, nr = min(rows, n2 - r0), t = threadIdx.x;
+    if (t < nr * n1) {
+        part += (long long)rhs * 2 * nk * nchunk * 4 * N + comp * N + off + r0 * n1 + t;
+        double2 sx = cmk(0.0, 0.0), sy = cmk(0.0, 0.0);
+        for (int b = 0; b < 2 * nk; ++b) {
+            double2 v = cmk(0.0, 0.0);  // a batch's sum by itself, as the plane kernel adds it up
+            for (int c = 0; c < nchunk; ++c) v = cadd(v, part[(b * nchunk + c) * 4 * N]);
+            if (b < nk) sx = cadd(sx, v); else sy = cadd(sy, v);
+        }
+        const double sgn = comp == 0 ? 1.0 : -1.0;
+        strip[t] = cscale(cmk(sx.x + sgn * sy.x, sx.y + sgn * sy.y), scale);
+    }
+    __syncthreads();
+    const int i1 = t / nr, r = t - i1 * nr;
+    if (i1 < n1) rho[(rhs * 4LL + comp) * N + off + i1 * n2 + r0 + r] = strip[r * n1 + i1];
+}
+
 // Right-hand side blockIdx.y: its rho (4 N), its scratch grid (N) and its W (4 N).
 // the charge component of rho into the scratch grid
 __global__ void k_copy_scale(const double2* rho, double2* dst, long long n) {
@@ -333,6 +358,57 @@ PlaneArgs plane_args(const System& s, const QSet& q) {
     return a;
 }
 
+// the system's arguments of the matrix-core plane kernels (whose axis 1 is the
+// plane's i2)
+MxArgs mx_args(const System& s, const QSet& q) {
+    MxArgs a{};
+    a.n1 = s.n2; a.n2 = s.n1; a.n3 = s.n3;
+    a.nk = q.nk; a.nb = s.nbnd; a.nitems = 2 * s.nbnd;
+    a.nb2 = 2 * q.nk;
+    a.tmod = q.tmod;
+    a.m1 = s.mmax[1];
+    a.m2 = s.mmax[0];
+    a.pitch = mx_pitch(a.n2);
+    a.sp = mx_spin_stride(a.n2, a.m1);
+    a.ncol_max = q.ncol_max;
+    a.ncol_u_max = q.ncol_u_max;
+    a.nchunk = s.ws.nchunk;
+    a.bpc = (s.nbnd + a.nchunk - 1) / a.nchunk;
+    a.fstride = 6 * s.N;
+    a.xcols = s.ws.xcols;
+    a.ucols = q.ucols;
+    a.colidx_x = q.d_colidx_kq;
+    a.colidx_u = q.d_colidx_u;
+    a.rho_part = s.ws.rho_part;
+    // grids without a table of their own keep it in the density partials, which
+    // are free once reduced and hold at least 8 N elements per right-hand side
+    a.fields = s.ws.fields ? s.ws.fields : s.ws.rho_part;
+    a.ureal = s.ureal_mode == 1 ? s.ureal : nullptr;
+    a.uslot = q.d_uslot;
+    a.ctab1 = s.ctab[1];
+    a.ctab2 = s.ctab[0];
+    a.twist1 = s.twist[1];
+    a.twist2 = s.twist[0];
+    return a;
+}
+
+// Whether a launch takes the matrix-core plane kernels: FP64, and planes and
+// spheres that they hold (mx_supported, mx_resident_reach, mx_column_reach).  Single precision
+// stays on the wave kernels (in FP32 the matrix-core apply takes 3.75 ms instead of
+// 4.90 at 48 x 48 x 180, 4 k, 104 bands, but rounds in another order).
+bool mx_path(const System& s, bool fp32) {
+    if (!s.mx || fp32) return false;
+    if (!plane_fixed_supported(s.n1, s.n2)) return true;
+    const int reach = s.ureal_mode == 1 ? mx_resident_reach(s.n1) : mx_column_reach(s.n1);
+    return std::max(s.mmax[0], s.mmax[1]) <= reach;
+}
+
+// bands a group, tuned per shape; the size class of the right-hand sides as for the z passes
+int mx_variant(int op, const System& s, const QSet& q, int nrhs) {
+    return tune_pick(op, tune_key(s.n1 * 1000 + s.n2, s.n3 * 2 + (s.ureal_mode == 1), s.nbnd, 2 * q.nk * 64 + rhs_class(nrhs)),
+                     kMxVariants);
+}
+
 int plane_threads(const System& s) {
     int NP = s.n1 * s.n2;
     int t = ((NP + kPts - 1) / kPts + 63) / 64 * 64;
@@ -368,7 +444,10 @@ static PlaneTabs plane_tabs(const System& s, const QSet& q) {
 void launch_density(const System& s, const QSet& q, hipStream_t st, bool fp32, int nrhs) {
     PlaneArgs a = plane_args(s, q);
     dim3 grid(s.n3, a.nchunk, 2 * q.nk * nrhs);
-    if (plane_fixed_supported(s.n1, s.n2)) {
+    int parts = a.nchunk;
+    if (mx_path(s, fp32)) {
+        parts = launch_plane_mx(true, mx_args(s, q), 2 * q.nk * nrhs, mx_variant(kTuneDensity, s, q, nrhs), st);
+    } else if (plane_fixed_supported(s.n1, s.n2)) {
         launch_plane_fixed(true, a, plane_tabs(s, q), grid, s.n1, s.n2, st, fp32);
     } else {
         TM_CHECK(!fp32, TM_EUNSUPPORTED, "single-precision plane kernels need a fixed-size plane");
@@ -382,6 +461,10 @@ void launch_density(const System& s, const QSet& q, hipStream_t st, bool fp32, i
     if (fp32) {
         TM_LAUNCH(k_density_reduce<float2>, rgrid, dim3(256), 0, st, a.rho_part32, s.ws.rho, s.N, q.nk, a.nchunk,
                   scale);
+    } else if (mx_path(s, fp32)) {
+        const int strips = (s.n2 + 256 / s.n1 - 1) / (256 / s.n1), rows = (s.n2 + strips - 1) / strips;
+        TM_LAUNCH(k_density_reduce_t, dim3((s.n2 + rows - 1) / rows, s.n3, 4 * nrhs), dim3(256), 0, st,
+                  s.ws.rho_part, s.ws.rho, s.n1, s.n2, s.n3, rows, q.nk, parts, scale);
     } else {
         TM_LAUNCH(k_density_reduce<double2>, rgrid, dim3(256), 0, st, s.ws.rho_part, s.ws.rho, s.N, q.nk, a.nchunk,
                   scale);
@@ -614,6 +697,12 @@ void launch_potential(const System& s, const QSet& q, hipStream_t st, int nrhs) 
 void launch_apply_planes(const System& s, const QSet& q, hipStream_t st, bool fp32, int nrhs) {
     PlaneArgs a = plane_args(s, q);
     dim3 grid(s.n3, a.nchunk, 2 * q.nk * nrhs);
+    if (mx_path(s, fp32)) {
+        const MxArgs m = mx_args(s, q);
+        launch_fields_mx(s.vrs, s.ws.W, const_cast<void*>(m.fields), m.n1, m.n2, m.n3, 4 * s.N, m.fstride, nrhs, st);
+        launch_plane_mx(false, m, 2 * q.nk * nrhs, mx_variant(kTuneApply, s, q, nrhs), st);
+        return;
+    }
     if (plane_fixed_supported(s.n1, s.n2)) {
         launch_plane_fixed(false, a, plane_tabs(s, q), grid, s.n1, s.n2, st, fp32);
         return;

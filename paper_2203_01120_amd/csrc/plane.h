@@ -97,6 +97,90 @@ bool zpass_fixed_supported(int n3);
 void launch_zpass_fixed(bool inverse, const ZPassArgs& a, int ncolmax, int nbatch, int n3, hipStream_t st,
                         bool fp32 = false);
 
+// radix plan of the fixed plane sizes; position p of a digit-reversed line holds
+// element sum_s d_s pre[s], p = sum_s d_s n / (pre[s] rad[s])
+struct CPlan {
+    int nrad;
+    int rad[8];
+    int pre[8];  // product of the radices before stage s
+};
+
+constexpr CPlan cplan(int n) {
+    CPlan p{};
+    p.nrad = 0;
+    int m = n, pre = 1;
+    const int order[4] = {4, 5, 3, 2};
+    for (int oi = 0; oi < 4; ++oi) {
+        int r = order[oi];
+        while (m % r == 0) {
+            p.rad[p.nrad] = r;
+            p.pre[p.nrad] = pre;
+            pre *= r;
+            ++p.nrad;
+            m /= r;
+        }
+    }
+    return p;
+}
+
+// arguments of the matrix-core plane kernels (planemx.hip)
+struct MxArgs {
+    int n1, n2, n3, nk, nb, nitems;
+    int nb2, tmod;               // see PlaneArgs
+    int m1, m2;                  // |m1|, |m2| of every sphere of the system, at most
+    int pitch, sp;               // row buffer: elements between rows, and between the spins
+    int ncol_max, ncol_u_max;
+    int nchunk, bpc;             // chunks of bands of the density partials, and bands in one
+    int cpb;                     // of them in a block (density)
+    int bb, bpb;                 // bands in a group, in a block (apply)
+    int rtiles;                  // row tiles of a group
+    int cwaves, rwaves;          // column and row waves of a block (density)
+    int nbatch, ny;              // batches, and blocks of one batch and plane
+    int cgroups;                 // blocks the columns are split over (density)
+    bool dbuf;                   // two row buffers (density)
+    long long fstride;           // elements between the field tables of right-hand sides
+    void* xcols;                 // T2 [batch][item][n3][ncol_max]
+    const double2* ucols;        // column path: [2 nk][item][n3][ncol_u_max]
+    const short* const* colidx_x;  // [n1 n2] column of the k+q sphere at a plane position, or -1
+    const short* const* colidx_u;  // the same for the ground-state sphere
+    void* rho_part;              // T2 [batch][chunk][4][N]
+    const void* fields;          // T2, laid out by launch_fields_mx
+    const double2* ureal;        // [slot][nb][n3][spin][digit-reversed row][column], or null: column path
+    const int* uslot;
+    const void *ctab1, *ctab2;   // T2 mx_constants of both axes
+    const void *twist1, *twist2; // T2 mx_twists of both axes
+};
+// row buffer: an odd pitch (a column's rows fall into distinct LDS banks), the
+// two spins of a column tile's rows 8 banks of 16 bytes apart
+__host__ __device__ constexpr int mx_pitch(int n2) { return n2 | 1; }
+__host__ __device__ constexpr int mx_spin_stride(int n2, int m1) {
+    return ((2 * m1 + 1) * mx_pitch(n2) + 7) / 16 * 16 + 8;
+}
+bool mx_supported(int n1, int n2, int m1, int m2);
+// The reach up to which they take the resident ground state's planes.  At 48 x
+// 48 a sphere that reaches 23 has 6 K steps, twice the products of the
+// half-filled one, and spills: 907 us an apply (48^3, 16 bands) against 756 us of
+// the wave kernels; reach 12 still 430 against 472.  The smaller planes stay
+// ahead up to the fullest sphere (20^3, reach 9: 132 both; 24^3, 11: 272 against
+// 318; 32^3, 15: 321 against 328).
+constexpr int mx_resident_reach(int n1) { return n1 == 48 ? 13 : n1 / 2 - 1; }
+// The same for the column path of those planes, where the ground state is
+// transformed too: half-filled spheres are ahead (24^3, reach 6: 236 us against
+// 267; 48^3, 11: 404 against 452), full ones are not (24^3, 9: 348 against 322;
+// 48^3, 18: 1277 against 817).  Other planes have no kernels with compile-time
+// sizes, and there the fullest is still ahead of the generic ones (45 x 40 x 40,
+// reach 19: 1010 against 1536; 60^3, 18: 1054 against 2320).
+constexpr int mx_column_reach(int n1) { return n1 == 8 ? 3 : 7 * n1 / 24; }
+// constants of the transforms of length n: rows m = 0 .. 23 of (cos, sin), see
+// planemx.hip, and the twists exp(-i pi m / n) (1 for odd n)
+std::vector<double2> mx_constants(int n);
+std::vector<double2> mx_twists(int n);
+constexpr int kMxVariants = 3;  // bands in a group: 1, 2, 4 at most
+// density: returns the partial sums of a batch that it wrote, a.nchunk at most
+int launch_plane_mx(bool density, const MxArgs& a, int nbatch, int variant, hipStream_t st);
+void launch_fields_mx(const double* vrs, const double2* W, void* fields, int n1, int n2, int n3, long long wstride,
+                      long long fstride, int nrhs, hipStream_t st);
+
 bool plane_fixed_supported(int n1, int n2);
 void launch_plane_fixed(bool density, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, int n1, int n2,
                         hipStream_t st, bool fp32 = false);

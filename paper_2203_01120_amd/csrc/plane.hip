@@ -1,18 +1,19 @@
-// Plane kernels with compile-time plane sizes (n1 x n2 <= 64 x 64).
+// Plane kernels with compile-time plane sizes (n1 x n2 <= 64 x 64) as radix
+// passes over LDS: the builder of the resident ground state, the wave kernels
+// that take single precision, and the kernels of planes that are too full for
+// the matrix-core ones (mx_resident_reach, mx_column_reach in plane.h).
 //
 // Same arithmetic as the generic k_density / k_apply_planes in apply.hip
 // (see the comments there for the physics); the organisation differs:
-//   * the four component planes of a band (x_up, x_dn, u_up, u_dn) sit in LDS
-//     together, so every radix pass of the 2D FFT serves four planes per
-//     barrier;
+//   * the planes of a band (x_up, x_dn, and on the column path u_up, u_dn) sit in
+//     LDS together, so every radix pass of the 2D FFT serves them per barrier;
 //   * plane sizes and radices are template constants (no integer division,
 //     fully unrolled butterflies); rows are padded to n2+1 entries so that
 //     row-wise accesses of neighbouring lanes fall in different LDS banks;
 //   * the first (row) direction of the inverse transform and the last
 //     direction of the forward transform run only over the rows that the
 //     plane-wave sphere occupies; the column direction reads inactive rows as
-//     zero instead of clearing them;
-//   * the local fields of a block's points stay in registers across bands.
+//     zero instead of clearing them.
 #include <type_traits>
 
 #include "fft_lds.h"
@@ -22,33 +23,9 @@ namespace tml {
 
 namespace {
 
-struct CPlan {
-    int nrad;
-    int rad[8];
-    int pre[8];  // product of the radices before stage s
-};
-
-constexpr CPlan cplan(int n) {
-    CPlan p{};
-    p.nrad = 0;
-    int m = n, pre = 1;
-    const int order[4] = {4, 5, 3, 2};
-    for (int oi = 0; oi < 4; ++oi) {
-        int r = order[oi];
-        while (m % r == 0) {
-            p.rad[p.nrad] = r;
-            p.pre[p.nrad] = pre;
-            pre *= r;
-            ++p.nrad;
-            m /= r;
-        }
-    }
-    return p;
-}
-
 constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// line addressing in the 4-plane LDS block
+// line addressing of planes in LDS
 template <int N1, int N2>
 struct Geom {
     static constexpr int N2P = N2 + 1;
@@ -420,23 +397,10 @@ __global__ void __launch_bounds__(NT) k_apply_t(PlaneArgs a, PlaneTabs t) {
     }
 }
 
-// Point order of a plane in the resident ground state, the per-apply field
-// table and the wave kernels' point-wise phases: column-major over the LDS
-// positions (p1, p2 digit-reversed), and within a column the row p1 = R blk + t
-// (R the last radix of n1's plan) at r = t (n1 / R) + blk.  The last column
-// stage works on butterflies of R consecutive rows, one per lane, so the lanes
-// of a column read consecutive points of this order.
-template <int N1>
-__device__ __forceinline__ int wrow(int r) {
-    constexpr CPlan cp = cplan(N1);
-    constexpr int R = cp.rad[cp.nrad - 1], BPC = N1 / R;
-    const int t = r / BPC, blk = r - t * BPC;
-    return blk * R + t;
-}
-
-// Resident real-space ground state: [slot][band][i3][spin][plane point], the
-// points in the order above, time reversal applied on the y side.
-
+// Resident real-space ground state: [slot][band][i3][spin][p2][i1], p2 the
+// digit-reversed position of i2, time reversal applied on the y side.  Both
+// readers take it in whole lines: the wave kernels the columns p2 of a wave one
+// after the other, the matrix-core kernels 8 neighbouring i1 of four rows i2.
 template <int N1, int N2, int NT>
 __global__ void __launch_bounds__(NT) k_ureal_t(PlaneArgs a, PlaneTabs t) {
     using K = PlaneKernel<N1, N2, NT, kU>;
@@ -453,12 +417,12 @@ __global__ void __launch_bounds__(NT) k_ureal_t(PlaneArgs a, PlaneTabs t) {
         K::inverse(m, a, b, b, b, n, i3, R);
         double2* out = a.ureal + (((long long)a.uslot[b] * a.nb + n) * a.n3 + i3) * 2 * G::NP;
         for (int idx = threadIdx.x; idx < G::NP; idx += NT) {
-            const int p2 = idx / N1, p1 = wrow<N1>(idx - p2 * N1);
+            const int p1 = idx / N2, p2 = idx - p1 * N2;
             const int o = p1 * G::N2P + p2;
             double2 uu = pl[o], ud = pl[G::PS + o];
             if (yside) time_reverse(uu, ud);
-            out[idx] = uu;
-            out[G::NP + idx] = ud;
+            out[p2 * N1 + m.perm1[p1]] = uu;
+            out[G::NP + p2 * N1 + m.perm1[p1]] = ud;
         }
         __syncthreads();
     }
@@ -691,6 +655,8 @@ struct WCols {
 // consecutive rows, no twiddles) and the first of the forward one, fused with
 // the point-wise work in registers: slot sl of a wave's CPW n1 / R butterflies
 // holds rows R blk .. R blk + R - 1 of column cc in both spin planes.
+// (lane order: the butterflies of a column in the order of their grid rows, so
+// that a column's lanes read consecutive points of the ground state and the fields)
 template <int N1, int N2, int CPW>
 struct WTail {
     static constexpr CPlan cp = cplan(N1);
@@ -699,15 +665,27 @@ struct WTail {
     static constexpr int SLOTS = CPW * BPC;
     static constexpr int IT = cdiv(SLOTS, 64);
     static_assert(cp.nrad >= 2, "the first column stage reads the row mask");
+    // butterfly blk of the g-th lane of a column: row t of the butterfly is grid
+    // row t BPC + g, at LDS position R blk + t
+    __device__ static int butterfly(int g) {
+        int blk = 0, w = BPC;
+#pragma unroll
+        for (int s = 0; s + 1 < cp.nrad; ++s) {
+            w /= cp.rad[s];
+            blk += g % cp.rad[s] * w;
+            g /= cp.rad[s];
+        }
+        return blk;
+    }
     int lo[IT];   // LDS offset (plane 0) of the slot's first row
-    int lq[IT];   // wave point of the slot's first row; row t at lq + t BPC
+    int lu[IT];   // resident ground state of the slot's first row; row t at lu + t BPC
     __device__ void init(int w, int lane) {
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int sl = min(lane + 64 * i, SLOTS - 1);
-            const int cc = sl / BPC, blk = sl - cc * BPC;
-            lo[i] = blk * R * Geom<N1, N2>::N2P + w * CPW + cc;
-            lq[i] = cc * N1 + blk;
+            const int cc = sl / BPC, g = sl - cc * BPC;
+            lo[i] = butterfly(g) * R * Geom<N1, N2>::N2P + w * CPW + cc;
+            lu[i] = (w * CPW + cc) * N1 + g;
         }
     }
     __device__ static bool live(int lane, int i) { return lane + 64 * i < SLOTS; }
@@ -1046,8 +1024,8 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a
     extern __shared__ double2 lds[];
     const typename K::Smem m = K::carve(lds);
     const T2* xcols = pick<T2>(a.xcols, a.xcols32);
-    // bt: side and k point of the batch; tb: its row in the sphere and slot tables
-    const int b = blockIdx.x, i3 = blockIdx.z, bt = b % a.nb2, tb = b % a.tmod;
+    // tb: the batch's row in the sphere and slot tables
+    const int b = blockIdx.x, i3 = blockIdx.z, tb = b % a.tmod;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     WTw<N1, T2> tw1{pick<T2>(t.tw1, t.tw1f)};
     // equal lengths share one table, so the two register sets are one
@@ -1059,7 +1037,7 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a
     const int nlw = K::wave_lines(nrx, w);
     const long long cs = (long long)a.n3 * a.ncol_max;
     // the side's resident slot, read once (the loop's stores could alias it)
-    const double2* ub = a.ureal + (long long)a.uslot[tb] * a.nb * a.n3 * 2 * G::NP + w * K::WPTS;
+    const double2* ub = a.ureal + (long long)a.uslot[tb] * a.nb * a.n3 * 2 * G::NP;
     TL tl;
     tl.init(w, lane);
     const typename K::Rows rl(m.rowbase, w, nlw, lane);
@@ -1089,8 +1067,8 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a
                 for (int i = 0; i < IT; ++i)
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        uu[i][r] = Cx<T2>::from(ur[tl.lq[i] + r * TL::BPC]);
-                        ud[i][r] = Cx<T2>::from(ur[G::NP + tl.lq[i] + r * TL::BPC]);
+                        uu[i][r] = Cx<T2>::from(ur[tl.lu[i] + r * TL::BPC]);
+                        ud[i][r] = Cx<T2>::from(ur[G::NP + tl.lu[i] + r * TL::BPC]);
                     }
             };
             if constexpr (EARLY) load_u();
@@ -1132,11 +1110,11 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a
         for (int i = 0; i < IT; ++i) {
             if (TL::live(lane, i)) {
                 const int sl = lane + 64 * i;
-                const int cc = sl / TL::BPC, blk = sl - cc * TL::BPC;
+                const int cc = sl / TL::BPC, g1 = sl - cc * TL::BPC;
                 const int g2 = m.perm2[w * CPW + cc];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int g = m.perm1[blk * R + r] * N2 + g2;
+                    const int g = (r * TL::BPC + g1) * N2 + g2;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) out[c * N + g] = acc[c][i][r];
                 }
@@ -1148,14 +1126,13 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a
 // Local fields, six complex values per point:
 //   (v + Bz, v - Bz), (Bx, By), W0 + Wz, W0 - Wz, Wx - i Wy, Wx + i Wy
 // (x side; the y side flips the sign of B and of the vector part of W), laid
-// out per plane i3 and LDS column p2 as [t][value][blk] for the row
-// p1 = R blk + t, so that the lanes holding the butterflies blk of the last
-// column stage read 16-lane runs, and a lane's 6 R values sit at small
+// out per plane i3 and LDS column p2 as [t][value][g] for the grid row
+// t (n1 / R) + g, so that the lanes of a column read runs, and a lane's 6 R values sit at small
 // constant offsets from one address.
 // (right-hand side blockIdx.z: its W and its table, wstride / fstride apart)
 template <int N1, int N2, class T2>
-__global__ void k_fields_w(const double* __restrict__ vrs, const double2* __restrict__ W, const int* perm1,
-                           const int* perm2, T2* __restrict__ F, int n3, long long wstride, long long fstride) {
+__global__ void k_fields_w(const double* __restrict__ vrs, const double2* __restrict__ W, const int* perm2,
+                           T2* __restrict__ F, int n3, long long wstride, long long fstride) {
     constexpr int NP = N1 * N2;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     const int i3 = blockIdx.y;
@@ -1163,11 +1140,10 @@ __global__ void k_fields_w(const double* __restrict__ vrs, const double2* __rest
     W += blockIdx.z * wstride;
     F += blockIdx.z * fstride;
     using TL = WTail<N1, N2, 1>;
-    const int p2 = idx / N1, r = idx - p2 * N1;
-    const int tt = r / TL::BPC, blk = r - tt * TL::BPC;
-    const int p1 = blk * TL::R + tt;
+    const int p2 = idx / N1, i1 = idx - p2 * N1;
+    const int tt = i1 / TL::BPC, blk = i1 - tt * TL::BPC;
     const long long N = (long long)NP * n3;
-    const long long g = (long long)i3 * NP + perm1[p1] * N2 + perm2[p2];
+    const long long g = (long long)i3 * NP + i1 * N2 + perm2[p2];
     const double v = vrs[g], bx = vrs[N + g], by = vrs[2 * N + g], bz = vrs[3 * N + g];
     const double2 w0 = W[g], wx = W[N + g], wy = W[2 * N + g], wz = W[3 * N + g];
     constexpr int B = TL::BPC;
@@ -1216,15 +1192,15 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_apply_w(PlaneArgs a, 
     const double2* ub = a.ureal + (long long)a.uslot[tb] * a.nb * a.n3 * 2 * G::NP + w * K::WPTS;
     const bool yside = bt >= a.nk;
     // the lane's points q = lane + 64 j of the wave (column cc, row position
-    // r = t B + blk in the point order): LDS offset, and field table offset
+    // i1 = t B + g): LDS offset, and field table offset
     int o[PPL], fo[PPL];
 #pragma unroll
     for (int j = 0; j < PPL; ++j) {
         const int q = min(lane + 64 * j, K::WPTS - 1);
-        const int cc = q / N1, r = q - cc * N1;
-        const int tt = r / B, blk = r - tt * B;
-        o[j] = (blk * TL::R + tt) * G::N2P + w * CPW + cc;
-        fo[j] = cc * 6 * N1 + tt * 6 * B + blk;
+        const int cc = q / N1, i1 = q - cc * N1;
+        const int tt = i1 / B, g = i1 - tt * B;
+        o[j] = (TL::butterfly(g) * TL::R + tt) * G::N2P + w * CPW + cc;
+        fo[j] = cc * 6 * N1 + tt * 6 * B + g;
     }
     const T2* fw = pick<T2>(a.fields, a.fields32) + (long long)(b / a.nb2) * a.fstride +
                    ((long long)i3 * N2 + w * CPW) * 6 * N1;
@@ -1343,45 +1319,28 @@ void launch_with_lds(F kernel, const char* name, size_t shm, dim3 grid, int nt, 
     check_launch(name);
 }
 
-// Variants of the FP64 wave plane kernels that the autotuner times, variant 0
-// being the hand-picked default: BT butterflies per load group, CPW columns
-// per wave, FCH row elements in flight per lane, fused first / last row
-// stages, loads issued ahead (the density: a band's ground state before its
-// row phase; the apply: the next band's row elements during this band's
-// forward row stage; all with two LDS buffers and no occupancy floor).  They
-// split the work differently and do the same arithmetic per point in the same
-// order, so their results are identical.
-template <int N1, int N2>
-struct WaveVariants {  // 8x8, 24x24, 32x32
+// Variants of the FP64 wave plane kernels (48 x 48) that the autotuner times:
+// BT butterflies per load group, and how far the apply loads ahead (1: the next
+// band's row elements during this band's forward row stage, 2: its ground state
+// too; the density loads a band's ground state before its row phase).  All with
+// 4 columns per wave, two LDS buffers, fused first / last row stages and no
+// occupancy floor.  They split the work differently and do the same arithmetic
+// per point in the same order, so their results are identical.  (Variants with
+// separate row stages are 10 % slower, and the compiler contracts their
+// multiply-adds differently: last bits that depend on the variant.)
+struct WaveVariants {
     static constexpr int n = 3;
-    static constexpr int bt[n] = {2, 1, 2}, cpw[n] = {4, 4, 4}, fch[n] = {1, 1, 1};
-    static constexpr bool fuse[n] = {false, false, true};
-    static constexpr int ahead[n] = {0, 0, 0};
-};
-template <>
-struct WaveVariants<48, 48> {
-    static constexpr int n = 9;
-    static constexpr int bt[n] = {2, 1, 4, 2, 2, 1, 1, 2, 1}, cpw[n] = {4, 4, 4, 4, 4, 4, 4, 4, 4},
-                         fch[n] = {1, 1, 1, 4, 1, 1, 1, 1, 1}, ahead[n] = {0, 0, 0, 0, 0, 0, 1, 1, 2};
-    static constexpr bool fuse[n] = {false, false, false, false, true, true, true, true, true};
-};
-template <>
-struct WaveVariants<20, 20> {
-    static constexpr int n = 5;
-    static constexpr int bt[n] = {2, 2, 1, 2, 2}, cpw[n] = {5, 4, 5, 10, 5}, fch[n] = {1, 1, 1, 1, 1};
-    static constexpr bool fuse[n] = {false, false, false, false, true};
-    static constexpr int ahead[n] = {0, 0, 0, 0, 0};
+    static constexpr int bt[n] = {1, 2, 1}, ahead[n] = {1, 1, 2};
 };
 
 template <int N1, int N2, int V>
 void launch_wave_one(bool density, const PlaneArgs& a, const PlaneTabs& t, dim3 wgrid, hipStream_t st) {
-    using VV = WaveVariants<N1, N2>;
-    constexpr int BT = VV::bt[V], CPW = VV::cpw[V], FCH = VV::fch[V];
-    constexpr bool FU = VV::fuse[V];
-    constexpr int AH = VV::ahead[V];
+    using VV = WaveVariants;
+    constexpr int BT = VV::bt[V], AH = VV::ahead[V], CPW = 4, FCH = 1;
+    constexpr bool FU = true;
     using K = WaveKernel<N1, N2, BT, CPW, double2, 2, FCH, FU>;
     if (density)
-        launch_with_lds(k_density_w<N1, N2, BT, CPW, double2, 2, 1, FCH, FU, (AH > 0)>, "k_density_w", K::bytes(),
+        launch_with_lds(k_density_w<N1, N2, BT, CPW, double2, 2, 1, FCH, FU, true>, "k_density_w", K::bytes(),
                         wgrid, K::NT, st, a, t);
     else
         launch_with_lds(k_apply_w<N1, N2, BT, CPW, double2, 2, 1, FCH, FU, AH>, "k_apply_w", K::bytes(), wgrid,
@@ -1400,11 +1359,10 @@ void launch_wave_v(bool density, int v, const PlaneArgs& a, const PlaneTabs& t, 
 // NT: threads of the block-synchronous kernels (column path, builder)
 template <int N1, int N2, int NT>
 void launch_t(int op, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, hipStream_t st, bool fp32) {
-    // FP64: the variants of WaveVariants, picked per shape by the autotuner
-    // (defaults: 4 columns per wave, 12 waves for 48 x 48 -- 3 columns and 16
-    // waves measured slower: idle lanes in the column stages and register
-    // spills at 128 VGPRs; one buffer with 6 or 8 columns, or 6 waves per SIMD,
-    // spill in FP64; 20 x 20 planes: 5 columns per wave).  Single precision
+    // FP64 (48 x 48): the variants of WaveVariants, picked per shape by the
+    // autotuner (3 columns per wave and 16 waves measured slower: idle lanes in
+    // the column stages and register spills at 128 VGPRs; one buffer with 6 or 8
+    // columns, or 6 waves per SIMD, spill in FP64).  Single precision
     // (fixed): the apply at 48 x 48 runs 6 columns per wave and 4 waves per
     // SIMD (2 blocks per CU in 2 x 81 KB of LDS, no spills): 7 % faster; the
     // density's row fill keeps all of a lane's loads in flight together
@@ -1433,7 +1391,7 @@ void launch_t(int op, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, hipStre
                                 WD::bytes(), wgrid, WD::NT, st, aw, t);
             } else {
                 TM_LAUNCH((k_fields_w<N1, N2, float2>), dim3((N1 * N2 + 255) / 256, a.n3, nrhs), dim3(256), 0, st,
-                          a.vrs, a.W, t.perm1, t.perm2, a.fields32, a.n3, a.wstride, a.fstride);
+                          a.vrs, a.W, t.perm2, a.fields32, a.n3, a.wstride, a.fstride);
                 launch_with_lds(k_apply_w<N1, N2, BTA, CPWA32, float2, NBUF32, MINWA32, FCHA32>, "k_apply_w32",
                                 WA::bytes(), wgrid, WA::NT, st, aw, t);
             }
@@ -1441,16 +1399,19 @@ void launch_t(int op, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, hipStre
         }
         // FP64: the variant the autotuner picked for this shape (plane, planes,
         // bands and sides, and the size class of the right-hand side count)
-        const long long key = tune_key(N1 * 1000 + N2, a.n3, a.nb, a.nb2 * 64 + rhs_class(nrhs));
-        if (op == kOpDensity) {
-            constexpr int NV = WaveVariants<N1, N2>::n;
-            launch_wave_v<N1, N2, NV - 1>(true, tune_pick(kTuneDensity, key, NV), aw, t, wgrid, st, nrhs);
+        if constexpr (N1 == 48) {
+            const long long key = tune_key(N1 * 1000 + N2, a.n3, a.nb, a.nb2 * 64 + rhs_class(nrhs));
+            constexpr int NV = WaveVariants::n;
+            if (op == kOpDensity) {
+                launch_wave_v<N1, N2, NV - 1>(true, tune_pick(kTuneDensity, key, NV), aw, t, wgrid, st, nrhs);
+            } else {
+                TM_CHECK(a.fields != nullptr, TM_EINVAL, "missing field table");
+                TM_LAUNCH((k_fields_w<N1, N2, double2>), dim3((N1 * N2 + 255) / 256, a.n3, nrhs), dim3(256), 0, st,
+                          a.vrs, a.W, t.perm2, a.fields, a.n3, a.wstride, a.fstride);
+                launch_wave_v<N1, N2, NV - 1>(false, tune_pick(kTuneApply, key, NV), aw, t, wgrid, st, nrhs);
+            }
         } else {
-            TM_CHECK(a.fields != nullptr, TM_EINVAL, "missing field table");
-            TM_LAUNCH((k_fields_w<N1, N2, double2>), dim3((N1 * N2 + 255) / 256, a.n3, nrhs), dim3(256), 0, st,
-                      a.vrs, a.W, t.perm1, t.perm2, a.fields, a.n3, a.wstride, a.fstride);
-            constexpr int NV = WaveVariants<N1, N2>::n;
-            launch_wave_v<N1, N2, NV - 1>(false, tune_pick(kTuneApply, key, NV), aw, t, wgrid, st, nrhs);
+            throw Error{TM_EUNSUPPORTED, "no FP64 wave kernel for this plane"};
         }
     } else {
         TM_CHECK(!fp32, TM_EUNSUPPORTED, "single-precision plane kernels need the resident ground state");

@@ -209,6 +209,7 @@ struct QSet {
     int** d_rows_u = nullptr;
     int* d_uslot = nullptr;       // [2nk] slot of each batch in the resident real-space ground state
     short** d_colidx_kq = nullptr;  // [2nk] plane position -> column of the k+q sphere, or -1
+    short** d_colidx_u = nullptr;   // the same for the ground-state spheres
     // lazily built caches
     double2* ucols = nullptr;     // z-transformed ground-state columns [b][nb*2][n3][ncol_u_max]
     size_t ucols_bytes = 0;
@@ -248,6 +249,12 @@ struct System {
     double2* tw[3] = {nullptr, nullptr, nullptr};
     float2* twf[3] = {nullptr, nullptr, nullptr};  // the same twiddles in single precision
     int* perm[3] = {nullptr, nullptr, nullptr};  // digit reversal of the in-place plane transforms
+    int mmax[2] = {0, 0};                        // |m1|, |m2| of every sphere, at most
+    bool mx = false;                             // the matrix-core plane kernels take this system
+    double2* ctab[2] = {nullptr, nullptr};       // their constants for both plane axes
+    double2* twist[2] = {nullptr, nullptr};      // and twists
+    float2* ctabf[2] = {nullptr, nullptr};       // the same in single precision
+    float2* twistf[2] = {nullptr, nullptr};
     // ground-state points (device)
     std::vector<double2*> evc;    // [npts] [nb][2][npw]
     std::vector<int> npw;
