@@ -961,7 +961,7 @@ static void apply_l_ready(System& s, QSet& q, const double2* in, double2* out, b
     const long long bstride = (long long)s.nbnd * 2 * q.npw_pad;
     launch_zpass_inv(s, q, false, in, bstride, 2 * s.nbnd, q.npw_pad, s.ws.xcols, st, fp32, nrhs);
     launch_density(s, q, st, fp32, nrhs);
-    launch_potential(s, q, st, nrhs);
+    launch_potential(s, q, st, fp32, nrhs);
     launch_apply_planes(s, q, st, fp32, nrhs);
     launch_zpass_fwd(s, q, s.ws.xcols, in, out, st, fp32, nrhs);
     launch_nonlocal(s, q, in, out, st, fp32, nrhs);

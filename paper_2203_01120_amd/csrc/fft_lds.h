@@ -143,6 +143,21 @@ __device__ inline void lds_fft_lines(double2* lds, int nlines, const LN& ln, int
     }
 }
 
+// Transform of length N with the radices of the plan (4s, then 5s, 3s, 2s),
+// with N and the radices known at compile time: P = product of the earlier radices
+constexpr int next_radix(int m) { return m % 4 == 0 ? 4 : m % 5 == 0 ? 5 : m % 3 == 0 ? 3 : 2; }
+
+// NL lines, NT threads: a thread takes at most ceil(NL N / R / NT) butterflies
+template <int N, int NL, int NT, int P = 1, class LN>
+__device__ __forceinline__ void ct_fft(double2* lds, const LN& ln, int estride, const double2* tw, int sign) {
+    if constexpr (P < N) {
+        constexpr int R = next_radix(N / P);
+        constexpr int BF = (NL * (N / R) + NT - 1) / NT;
+        fft_pass<R, BF>(lds, NL, ln, estride, N, P, tw, sign);
+        ct_fft<N, NL, NT, P * R>(lds, ln, estride, tw, sign);
+    }
+}
+
 // lines l * lstride
 __device__ inline void lds_fft(double2* lds, int nlines, int lstride, int estride, const FFTPlan& pl,
                                int sign) {

@@ -181,6 +181,15 @@ int launch_plane_mx(bool density, const MxArgs& a, int nbatch, int variant, hipS
 void launch_fields_mx(const double* vrs, const double2* W, void* fields, int n1, int n2, int n3, long long wstride,
                       long long fstride, int nrhs, hipStream_t st);
 
+// response density and potential by planes and columns (potential.hip)
+constexpr long long kPotLdsMax = 1024;  // grids up to here: k_potential_lds
+bool pot_planes_supported(const System& s);
+// partials -> ws.rho, and the charge transformed in its planes -> ws.work
+void launch_rho_planes(const System& s, const void* part, bool single, int nk, int nparts, bool turned, double scale,
+                       int nrhs, hipStream_t st);
+// ws.work, ws.rho -> W, or the field tables if fields is given
+void launch_pot_planes(const System& s, const QSet& q, double2* fields, long long fstride, int nrhs, hipStream_t st);
+
 bool plane_fixed_supported(int n1, int n2);
 void launch_plane_fixed(bool density, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, int n1, int n2,
                         hipStream_t st, bool fp32 = false);

@@ -328,7 +328,7 @@ void launch_zpass_fwd(const System& s, const QSet& q, const double2* cols, const
 void launch_fft3d_full(const System& s, double2* data, int sign, hipStream_t st, int nrhs = 1);
 // apply.hip
 void launch_density(const System& s, const QSet& q, hipStream_t st, bool fp32 = false, int nrhs = 1);
-void launch_potential(const System& s, const QSet& q, hipStream_t st, int nrhs = 1);
+void launch_potential(const System& s, const QSet& q, hipStream_t st, bool fp32 = false, int nrhs = 1);
 void launch_apply_planes(const System& s, const QSet& q, hipStream_t st, bool fp32 = false, int nrhs = 1);
 void launch_ureal(const System& s, const QSet& q, hipStream_t st);
 void launch_fxc_setup(System& s, const double* rho_plane, hipStream_t st);

@@ -105,3 +105,29 @@ def test_many_lanes_equal_single_chains():
                     assert np.array_equal(lane[key], one[key]), (d, key)
     finally:
         tm.tm_system_destroy(h)
+
+
+@pytest.mark.parametrize("n1,n2,n3", [(8, 8, 16), (8, 16, 9), (10, 9, 125), (6, 5, 300), (64, 64, 24), (128, 30, 6),
+                                      (24, 24, 20), (32, 32, 32), (20, 20, 25)])
+def test_potential_at_its_limits(n1, n2, n3):
+    """The response potential where its launches change: the largest grid of one
+    block and the first past it, the longest columns in LDS and the first too
+    long, 16 columns a block, the largest and a long plane, and the compile-time
+    plane and column lengths apart and together; an apply to 1e-12 as above."""
+    import torch
+    import paper_2203_01120_amd as tm
+    prob = _problem(n1, n2, n3, 2, 2, 3, 29)
+    h = tm.tm_system_create(desc_from_problem(prob))
+    try:
+        say(f"potential {n1} x {n2} x {n3}")
+        info = tm.tm_qset_info_get(h, 0)
+        x = prob.random_projected(1)
+        xin = to_gpu(x, info["npw_pad"])
+        out = torch.empty_like(xin)
+        tm.tm_liouvillian_apply(h, 0, xin, out)
+        torch.cuda.synchronize()
+        got, _ = from_gpu(out, (2, 1, prob.nb, 2, info["npw_pad"]), prob.npw_pad)
+        err = rel_err(got, prob.apply(x))
+        assert err <= 1e-12, err
+    finally:
+        tm.tm_system_destroy(h)
