@@ -500,6 +500,13 @@ void build_qset(System& s, const tm_system_desc* d, int iq, int npw_pad, QSet& q
     q.d_eps = upload_table(s, t_eps);
     q.d_occ = upload_table(s, t_occ);
     q.d_vkb = upload_table(s, t_vkb);
+    if (s.nproj > 0) {
+        std::vector<double2*> t_gram(2 * nk);
+        double2* gram = dev_alloc<double2>(s, (size_t)2 * nk * 2 * s.nproj * nb);
+        for (int b = 0; b < 2 * nk; ++b) t_gram[b] = gram + (size_t)b * 2 * s.nproj * nb;
+        q.d_gram = upload_table(s, t_gram);
+        launch_gram(s, q, st);
+    }
     q.d_maps = upload_table(s, t_maps);
     q.hq = dev_alloc<double>(s, s.N);
     launch_coulomb_setup(s, q, st);
@@ -681,6 +688,7 @@ static QSet& lane_group(System& s, const std::vector<int>& iqs) {
     g->d_eps = cat_table(s, iqs, &QSet::d_eps, nb2);
     g->d_occ = cat_table(s, iqs, &QSet::d_occ, nb2);
     g->d_vkb = cat_table(s, iqs, &QSet::d_vkb, nb2);
+    if (s.nproj > 0) g->d_gram = cat_table(s, iqs, &QSet::d_gram, nb2);
     g->d_nrows_kq = cat_table(s, iqs, &QSet::d_nrows_kq, nb2);
     g->d_rmask_kq = cat_table(s, iqs, &QSet::d_rmask_kq, nb2);
     g->d_rows_kq = cat_table(s, iqs, &QSet::d_rows_kq, nb2);
@@ -964,8 +972,7 @@ static void apply_l_ready(System& s, QSet& q, const double2* in, double2* out, b
     launch_potential(s, q, st, fp32, nrhs);
     launch_apply_planes(s, q, st, fp32, nrhs);
     launch_zpass_fwd(s, q, s.ws.xcols, in, out, st, fp32, nrhs);
-    launch_nonlocal(s, q, in, out, st, fp32, nrhs);
-    launch_project(s, q, out, st, fp32, nrhs);
+    launch_nonlocal_project(s, q, in, out, st, fp32, nrhs);
 }
 
 static void start_vectors_raw(System& s, int iq, int dir, double2* u, double2* v, hipStream_t st) {
@@ -1846,7 +1853,7 @@ int tm_system_footprint(const tm_system_desc* d, tm_memory_info* out) {
                 // occupied partners, projector tables (the point's and the padded copy),
                 // restriction maps, kinetic energies, Miller indices, eigenvalues,
                 // plane-position column indices, three sphere maps
-                tables += 2.0 * nb * 2 * P * sizeof(double2) + (double)d->nproj * (P + npw) * sizeof(double2) +
+                tables += 2.0 * nb * 2 * P * sizeof(double2) + (double)d->nproj * (P + npw + 4.0 * nb) * sizeof(double2) +
                           (2 * P + npw) * sizeof(int) + P * sizeof(double) + 3 * npw * sizeof(int) +
                           2.0 * nb * sizeof(double) + 3 * NP * sizeof(short) +
                           2.0 * (npw + d->npw[r[0]] + d->npw[r[1]] + ncol[r[2]] + ncol[r[0]] + ncol[r[1]] + 3) *

@@ -392,6 +392,264 @@ __global__ void __launch_bounds__(1024) k_gemm_update(GemmUpd g) {
     }
 }
 
+// ---- the nonlocal term and the projector of an apply together (FP64)
+// With G = O^dag beta (per q set, laid out once), S = O^dag (phi + beta W) =
+// O^dag phi + G W: both contractions read the apply's x and phi as they are, and
+// one update adds beta W - O S.  phi is read twice and written once instead of
+// four times and twice, in 3 to 5 launches instead of 5 to 7.  us of the stage,
+// before -> after: 20^3, 8 bands 31 -> 13; 24^3, 16 bands, 4 k 56 -> 21; 45 x 40 x 50, 12
+// bands 103 -> 24; 48 x 48 x 96, 64 bands 143 -> 101.  48 x 48 x 180, 104 bands, 4 k: 794 ->
+// 749, where the contractions and the update run at 60 to 72 TFLOP/s of the 72.6
+// of a large matrix product and what is saved is the summing in between.
+
+// Contractions of up to two pairs of operands, few output tiles each: a block
+// per (tile of either, K split, batch), whose four waves take groups of KU
+// steps in turn (as many loads in flight) and add up in LDS.  A split of 64 is
+// one group a wave, and at most 32 splits bound the summing that follows.
+constexpr int kPairWaves = 4, kPairKU = 4, kPairK = 16 * kPairWaves, kPairSplits = 32;
+
+__global__ void __launch_bounds__(64 * kPairWaves) k_cn_pair(GemmCN g0, GemmCN g1, int tiles0) {
+    __shared__ double2 red[kPairWaves][256];
+    const bool second = (int)blockIdx.x >= tiles0;
+    const GemmCN& g = second ? g1 : g0;
+    const int tile = second ? blockIdx.x - tiles0 : blockIdx.x;
+    const int b = blockIdx.z, ks = blockIdx.y;
+    if (ks >= g.ksplit) return;
+    const int m0 = (tile / g.nt) * 16, n0 = (tile % g.nt) * 16;
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, kk = l >> 4;
+    const double2* A = g.A_tab[b % g.amod];
+    const double2* B = g.B_base + (long long)b * g.b_bstride;
+    const int kbeg = ks * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+    v4d cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
+    const bool arow = (m0 + i) < g.M, brow = (n0 + i) < g.Nn;
+    const double2* Ap = A + (long long)(m0 + i) * g.lda;
+    const double2* Bp = B + (long long)(n0 + i) * g.ldb;
+    for (int k = kbeg + 4 * kPairKU * w; k < kend; k += kPairK) {
+        double2 a[kPairKU], bv[kPairKU];
+#pragma unroll
+        for (int u = 0; u < kPairKU; ++u) {
+            const int kx = k + 4 * u + kk;
+            a[u] = gload((arow && kx < kend) ? Ap + kx : &g_zero2);
+            bv[u] = gload((brow && kx < kend) ? Bp + kx : &g_zero2);
+        }
+#pragma unroll
+        for (int u = 0; u < kPairKU; ++u) {
+            cr = mfma(a[u].x, bv[u].x, cr);
+            cr = mfma(a[u].y, bv[u].y, cr);
+            ci = mfma(a[u].x, bv[u].y, ci);
+            ci = mfma(-a[u].y, bv[u].x, ci);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[w][(4 * v + kk) * 16 + i] = cmk(cr[v], ci[v]);
+    __syncthreads();
+    const int m = m0 + threadIdx.x / 16, n = n0 + (threadIdx.x & 15);
+    if (m < g.M && n < g.Nn) {
+        double2 sum = red[0][threadIdx.x];
+#pragma unroll
+        for (int v = 1; v < kPairWaves; ++v) sum = cadd(sum, red[v][threadIdx.x]);
+        g.part[(((long long)b * g.ksplit + ks) * g.M + m) * g.Nn + n] = sum;
+    }
+}
+
+// G[(s, i)][m] = sum_k conj(occ[m][s][k]) vkb[i][k] of batch blockIdx.z; a block
+// per 16 x 16 tile and spin, its waves take interleaved slices of K
+__global__ void __launch_bounds__(64 * kSmallWaves) k_gram(const double2* const* occ, const double2* const* vkb,
+                                                           double2* const* gram, int nb, int nproj, int P) {
+    __shared__ double2 red[kSmallWaves][256];
+    const int b = blockIdx.z, sp = blockIdx.y, nt = (nproj + 15) / 16;
+    const int m0 = blockIdx.x / nt * 16, n0 = blockIdx.x % nt * 16;
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, kk = l >> 4;
+    v4d cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
+    const bool arow = (m0 + i) < nb, brow = (n0 + i) < nproj;
+    const double2* Ap = occ[b] + ((long long)(m0 + i) * 2 + sp) * P;
+    const double2* Bp = vkb[b] + (long long)(n0 + i) * P;
+    for (int k = 4 * w; k < P; k += 4 * kSmallWaves) {
+        const int kx = k + kk;
+        const double2 a = gload(arow && kx < P ? Ap + kx : &g_zero2), v = gload(brow && kx < P ? Bp + kx : &g_zero2);
+        cr = mfma(a.x, v.x, cr);
+        cr = mfma(a.y, v.y, cr);
+        ci = mfma(a.x, v.y, ci);
+        ci = mfma(-a.y, v.x, ci);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[w][(4 * v + kk) * 16 + i] = cmk(cr[v], ci[v]);
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        const int m = m0 + threadIdx.x / 16, n = n0 + (threadIdx.x & 15);
+        double2 sum = red[0][threadIdx.x];
+        for (int v = 1; v < kSmallWaves; ++v) sum = cadd(sum, red[v][threadIdx.x]);
+        if (m < nb && n < nproj) gram[b][((long long)sp * nproj + n) * nb + m] = sum;
+    }
+}
+
+// Sums of the partials of up to two contractions; 32 elements of 8 slices of the
+// splits a block, added up in slice order.
+__global__ void __launch_bounds__(256) k_reduce_pair(const double2* p0, double2* o0, int ks0, long long mn0, const double2* p1,
+                                                     double2* o1, int ks1, long long mn1, int blocks0) {
+    __shared__ double2 red[8][32];
+    const bool second = (int)blockIdx.x >= blocks0;
+    const long long mn = second ? mn1 : mn0;
+    const int ks = second ? ks1 : ks0, b = blockIdx.y, e = threadIdx.x & 31, sl = threadIdx.x >> 5;
+    const long long el = (long long)(second ? blockIdx.x - blocks0 : blockIdx.x) * 32 + e;
+    const double2* p = (second ? p1 : p0) + (long long)b * ks * mn + el;
+    double2 sum = cmk(0.0, 0.0);
+    if (el < mn) {
+#pragma unroll 4
+        for (int k = sl; k < ks; k += 8) sum = cadd(sum, p[k * mn]);
+    }
+    red[sl][e] = sum;
+    __syncthreads();
+    if (sl == 0 && el < mn) {
+#pragma unroll
+        for (int v = 1; v < 8; ++v) sum = cadd(sum, red[v][e]);
+        ((second ? o1 : o0) + (long long)b * mn)[el] = sum;
+    }
+}
+
+// The coefficients of the update, for columns n of 8 bands of batch blockIdx.y:
+//   W[i][(n,s)] = sum_j sum_t D[i][j][s][t] B[j][(n,t)],
+//   T[m][n] = -(S[m][n] + sum_s sum_i G[(s,i)][m] W[i][(n,s)]),
+// B and S being sums of ksb and kss partials (added up here: slices of them by
+// threads that the elements leave over, then the slices in order).  No
+// projectors: T = -S.
+constexpr int kCoefCols = 8, kCoefThreads = 512;
+struct Coef {
+    const double2 *Bp, *Sp;   // partials [b][ks][nproj][2 nb], [b][ks][nb][nb]
+    int ksb, kss;
+    const double2* D;
+    const double2* const* G;  // of batch b % tmod
+    int tmod, nproj, nb;
+    double2 *W, *T;
+};
+
+__global__ void __launch_bounds__(kCoefThreads) k_coefficients(Coef c) {
+    extern __shared__ double2 lds[];
+    const int nb = c.nb, np = c.nproj, b = blockIdx.y, n0 = blockIdx.x * kCoefCols;
+    const int eb = np * 2 * kCoefCols, es = nb * kCoefCols, E = eb + es;
+    const int slices = E < kCoefThreads ? kCoefThreads / E : 1;
+    double2* B = lds;            // [j][(n,t)]
+    double2* S = lds + eb;       // [m][n]
+    double2* Ws = lds + E;       // [i][(n,s)]
+    double2* red = Ws + eb;      // slices > 1: [slice][E]
+    const double2* bp = c.Bp + (long long)b * c.ksb * np * 2 * nb;
+    const double2* sp = c.Sp + (long long)b * c.kss * nb * nb;
+    for (int t = threadIdx.x; t < slices * E; t += kCoefThreads) {
+        const int sl = t / E, e = t - sl * E;
+        const bool isB = e < eb;
+        const int r = isB ? e / (2 * kCoefCols) : (e - eb) / kCoefCols;
+        const int col = isB ? e - r * 2 * kCoefCols : e - eb - r * kCoefCols;
+        const bool in = isB ? 2 * n0 + col < 2 * nb : n0 + col < nb;
+        double2 sum = cmk(0.0, 0.0);
+        if (in) {
+            const double2* p = isB ? bp + (long long)r * 2 * nb + 2 * n0 + col : sp + (long long)r * nb + n0 + col;
+            const long long st = isB ? (long long)np * 2 * nb : (long long)nb * nb;
+            const int ks = isB ? c.ksb : c.kss;
+#pragma unroll 4
+            for (int k = sl; k < ks; k += slices) sum = cadd(sum, p[k * st]);
+        }
+        if (slices > 1) red[t] = sum;
+        else lds[e] = sum;
+    }
+    __syncthreads();
+    if (slices > 1) {
+        for (int e = threadIdx.x; e < E; e += kCoefThreads) {
+            double2 sum = red[e];
+            for (int v = 1; v < slices; ++v) sum = cadd(sum, red[v * E + e]);
+            lds[e] = sum;
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < eb; e += kCoefThreads) {
+        const int i = e / (2 * kCoefCols), col = e - i * 2 * kCoefCols, s = col & 1;
+        const double2* D = c.D + ((long long)i * np * 2 + s) * 2;
+        double2 w = cmk(0.0, 0.0);
+        for (int j = 0; j < np; ++j)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) w = cadd(w, cmul(D[j * 4 + t], B[j * 2 * kCoefCols + col - s + t]));
+        Ws[e] = w;
+        if (2 * n0 + col < 2 * nb) c.W[((long long)b * np + i) * 2 * nb + 2 * n0 + col] = w;
+    }
+    __syncthreads();
+    const double2* G = np > 0 ? c.G[b % c.tmod] : nullptr;
+    for (int e = threadIdx.x; e < es; e += kCoefThreads) {
+        const int m = e / kCoefCols, n = e - m * kCoefCols;
+        double2 t = S[e];
+        for (int s = 0; s < 2; ++s)
+#pragma unroll 4
+            for (int i = 0; i < np; ++i) t = cadd(t, cmul(G[((long long)s * np + i) * nb + m], Ws[i * 2 * kCoefCols + 2 * n + s]));
+        if (n0 + n < nb) c.T[((long long)b * nb + m) * nb + n0 + n] = cmk(-t.x, -t.y);
+    }
+}
+
+// Y[n][(s,k)] = os (Y + sum_i W[i][(n,s)] vkb[i][k] + sum_m T[m][n] occ[m][(s,k)]):
+// the steps of both sums one after the other, grouped as in k_gemm_update<U>.
+struct UpdPair {
+    double2* Y;
+    const double2 *W, *T;
+    const double2 *const *vkb, *const *occ;  // of batch b % tmod
+    int tmod, nproj, nb, P, nk;
+    double os_x, os_y;
+};
+
+template <int U>
+__global__ void __launch_bounds__(1024) k_update_pair(UpdPair g) {
+    const int b = blockIdx.z, sp = blockIdx.x, nb = g.nb, P = g.P;
+    const int n0 = (threadIdx.x >> 6) * 16, k0 = blockIdx.y * 16;
+    const int l = threadIdx.x & 63, i = l & 15, kk = l >> 4;
+    const bool ncol = n0 + i < nb, kcol = k0 + i < P;
+    const double os = b % (2 * g.nk) < g.nk ? g.os_x : g.os_y;
+    const double2* A0 = g.nproj > 0 ? g.vkb[b % g.tmod] + k0 + i : nullptr;
+    const double2* A1 = g.occ[b % g.tmod] + (long long)sp * P + k0 + i;
+    const double2* C0 = g.W + (long long)b * g.nproj * 2 * nb + 2 * (n0 + i) + sp;
+    const double2* C1 = g.T + (long long)b * nb * nb + n0 + i;
+    double2* Y = g.Y + (long long)b * nb * 2 * P + (long long)sp * P + k0 + i;
+    const int t0 = (g.nproj + 3) / 4, t1 = t0 + (nb + 3) / 4;
+    v4d dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+    auto load = [&](int t, double2* c, double2* a) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int st = t + u;
+            const bool first = st < t0;
+            const int m = 4 * (first ? st : st - t0) + kk;
+            const bool in = m < (first ? g.nproj : nb);
+            c[u] = gload(in && ncol ? (first ? C0 + m * 2 * nb : C1 + m * nb) : &g_zero2);
+            a[u] = gload(in && kcol ? (first ? A0 + (long long)m * P : A1 + (long long)m * 2 * P) : &g_zero2);
+        }
+    };
+    auto products = [&](int t, const double2* c, const double2* a) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t + u < t1) {
+                dr = mfma(c[u].x, a[u].x, dr);
+                dr = mfma(-c[u].y, a[u].y, dr);
+                di = mfma(c[u].x, a[u].y, di);
+                di = mfma(c[u].y, a[u].x, di);
+            }
+        }
+    };
+    DVec2 ycur[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int n = n0 + 4 * v + kk;
+        const double2* py = (n < nb && kcol) ? Y + (long long)n * 2 * P : &g_zero2;
+        ycur[v] = *(const GlobalD2*)py;
+    }
+    double2 c0[U], a0[U], c1[U], a1[U];
+    load(0, c0, a0);
+    for (int t = 0; t < t1; t += 2 * U) {
+        load(t + U, c1, a1);
+        products(t, c0, a0);
+        load(t + 2 * U, c0, a0);
+        products(t + U, c1, a1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int n = n0 + 4 * v + kk;
+        if (n < nb && kcol) Y[(long long)n * 2 * P] = cmk(os * (ycur[v].x + dr[v]), os * (ycur[v].y + di[v]));
+    }
+}
+
 // W[b][i][(n,s)] = sum_j sum_t D[i][j][s][t] Bm[b][j][(n,t)]
 __global__ void k_dmat(const double2* Bm, const double2* D, double2* Wm, int nproj, int nb, int nbatch) {
     long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -505,6 +763,104 @@ void run_gemm_cn(const System& s, const double2* const* A_tab, int amod, int lda
                        out, g.ksplit, mn, nrhs * nbatch);
 }
 
+// one contraction of the pair: operands and K split (cap: partials of a right-hand side)
+GemmCN pair_side(const System& s, const double2* const* A_tab, int amod, const double2* B_base, long long b_bstride, int ld,
+                 int M, int Nn, int nbatch, long long cap, bool& staged) {
+    GemmCN g{};
+    g.A_tab = A_tab;
+    g.amod = amod;
+    g.lda = g.ldb = g.K = ld;
+    g.B_base = B_base;
+    g.b_bstride = b_bstride;
+    g.M = M;
+    g.Nn = Nn;
+    g.nt = (Nn + 15) / 16;
+    staged = cn_lds_fits(M, Nn);
+    if (staged) {
+        constexpr int kTargets[3] = {1024, 512, 2048};  // as in run_gemm_cn
+        g.kchunk = cn_lds_kchunk(ld, nbatch, kTargets[tune_pick(kTuneGemm, tune_key(M, Nn, nbatch), 3)]);
+    } else {
+        const int splits = (int)std::max<long long>(1, std::min<long long>(kPairSplits, cap / ((long long)nbatch * M * Nn)));
+        g.kchunk = std::max(kPairK, ((ld + splits - 1) / splits + kPairK - 1) / kPairK * kPairK);
+    }
+    g.ksplit = (ld + g.kchunk - 1) / g.kchunk;
+    return g;
+}
+
+void launch_staged(const GemmCN& g, int nbatch, hipStream_t st) {
+    const int mt = (g.M + 15) / 16;
+    const size_t shm = (size_t)(mt + g.nt) * 16 * (kCnChunk + 1) * 16;
+    TM_CHECK(hipFuncSetAttribute((const void*)k_gemm_cn_lds<double>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) ==
+                 hipSuccess,
+             TM_EDEVICE, "cannot raise the LDS limit of k_gemm_cn_lds");
+    TM_LAUNCH(k_gemm_cn_lds<double>, dim3(g.ksplit, nbatch), dim3(kCnThreads), shm, st, g, mt);
+}
+
+size_t coef_lds(int nproj, int nb) {
+    const int eb = nproj * 2 * kCoefCols, E = eb + nb * kCoefCols;
+    return (size_t)(E + eb + (E < kCoefThreads ? kCoefThreads / E * E : 0)) * sizeof(double2);
+}
+
+// phi <- os (phi + beta D beta^dag x - O O^dag (phi + beta D beta^dag x)), FP64;
+// x null: the projector alone.  The columns of the plane kernels are free here
+// and hold the partials of B and T.  False where they are too small for them:
+// the terms go one after the other then.  (The K splits and the choice depend on
+// the shape of one right-hand side, so that each is summed as when alone.)
+bool run_pair(const System& s, const QSet& q, const double2* x, double2* phi, double osx, double osy, int nrhs,
+              hipStream_t st) {
+    const int nb = s.nbnd, P = q.npw_pad, nbatch = 2 * q.nk, all = nbatch * nrhs, np = x ? s.nproj : 0;
+    const long long bstride = (long long)nb * 2 * P;
+    if (coef_lds(np, nb) > 150 * 1024) return false;
+    bool sb = false, ss = false;
+    const long long mns = (long long)nb * nb, mnb = (long long)np * 2 * nb;
+    const long long T = nbatch * mns, room = (long long)(s.ws.cap_xcols / s.ws.width) - T - nbatch * mnb;
+    GemmCN gs = pair_side(s, (const double2* const*)q.d_occ, q.tmod, phi, bstride, 2 * P, nb, nb, nbatch,
+                          (long long)(s.ws.cap_gpart / s.ws.width), ss);
+    GemmCN gb{};
+    if (np > 0) gb = pair_side(s, q.d_vkb, q.tmod, x, bstride, P, np, 2 * nb, nbatch, room, sb);
+    const long long parts = nbatch * gb.ksplit * mnb;
+    if (parts > room) return false;
+    // more elements than a block has threads: their sums in a launch of their own
+    const bool sums = (gs.ksplit > 1 || gb.ksplit > 1) && (np * 2 + nb) * kCoefCols > kCoefThreads;
+    TM_CHECK((size_t)all * gs.ksplit * mns <= s.ws.cap_gpart, TM_EINVAL, "GEMM partial buffer too small");
+    double2* t = s.ws.xcols;
+    gb.part = t + nrhs * T;
+    gs.part = s.ws.gpart;
+    double2* bred = gb.part + nrhs * parts;
+    const int tiles_b = np > 0 ? (np + 15) / 16 * gb.nt : 0, tiles_s = (nb + 15) / 16 * gs.nt;
+    if (ss) launch_staged(gs, all, st);
+    if (sb) launch_staged(gb, all, st);
+    if (!ss || (np > 0 && !sb)) {
+        const int tb = sb ? 0 : tiles_b, ts = ss ? 0 : tiles_s;
+        const int ks = std::max(tb > 0 ? gb.ksplit : 0, ts > 0 ? gs.ksplit : 0);
+        TM_LAUNCH(k_cn_pair, dim3(tb + ts, ks, all), dim3(64 * kPairWaves), 0, st, gb, gs, tb);
+    }
+    Coef c{gb.part, gs.part, gb.ksplit, gs.ksplit, s.dvan, q.d_gram, q.tmod, np, nb, s.ws.gsmall, t};
+    if (sums) {
+        const int blocks_s = (int)((mns + 31) / 32), blocks_b = (int)((mnb + 31) / 32);
+        TM_LAUNCH(k_reduce_pair, dim3(blocks_s + blocks_b, all), dim3(256), 0, st, gs.part, t, gs.ksplit, mns, gb.part, bred,
+                  gb.ksplit, mnb, blocks_s);
+        c.Bp = bred;
+        c.Sp = t;
+        c.ksb = c.kss = 1;
+    }
+    const size_t shm = coef_lds(np, nb);
+    TM_CHECK(hipFuncSetAttribute((const void*)k_coefficients, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) ==
+                 hipSuccess,
+             TM_EDEVICE, "cannot raise the LDS limit of k_coefficients");
+    TM_LAUNCH(k_coefficients, dim3((nb + kCoefCols - 1) / kCoefCols, all), dim3(kCoefThreads), shm, st, c);
+    UpdPair u{phi, c.W, t, q.d_vkb, (const double2* const*)q.d_occ, q.tmod, np, nb, P, q.nk, osx, osy};
+    const int ntile = (nb + 15) / 16;
+    TM_CHECK(ntile <= 16, TM_EUNSUPPORTED, "more than 256 output columns per batch");
+    const dim3 grid(2, (P + 15) / 16, all);
+    if (tune_pick(kTuneUpd, tune_key(nb, nb, nbatch), 3) == 1) {
+        TM_LAUNCH(k_update_pair<2>, grid, dim3(64 * ntile), 0, st, u);
+    } else {
+        TM_LAUNCH(k_update_pair<3>, grid, dim3(64 * ntile), 0, st, u);
+    }
+    return true;
+}
+
 void run_gemm_update(double2* Y, long long y_bstride, int ldy, const double2* C, long long c_bstride, int ldc,
                      const double2* const* A_tab, int tmod, int lda, int Nout, int K, int Minner, double cs,
                      double osx, double osy, int nk, int nrhs, hipStream_t st, bool f32 = false) {
@@ -551,7 +907,21 @@ size_t gemm_partial_elems(int nbatch, int M, int Nn, int K) {
     return (size_t)nbatch * ks * M * Nn;
 }
 
+// G of k_coefficients, for the batches of a q set
+void launch_gram(const System& s, const QSet& q, hipStream_t st) {
+    const int tiles = (s.nbnd + 15) / 16 * ((s.nproj + 15) / 16);
+    TM_LAUNCH(k_gram, dim3(tiles, 2, 2 * q.nk), dim3(64 * kSmallWaves), 0, st, (const double2* const*)q.d_occ,
+              (const double2* const*)q.d_vkb, q.d_gram, s.nbnd, s.nproj, q.npw_pad);
+}
+
 // x and out hold nrhs BR vectors back to back
+void launch_nonlocal_project(const System& s, const QSet& q, const double2* x, double2* out, hipStream_t st, bool f32,
+                             int nrhs) {
+    if (!f32 && run_pair(s, q, x, out, 1.0, -1.0, nrhs, st)) return;
+    launch_nonlocal(s, q, x, out, st, f32, nrhs);
+    launch_project(s, q, out, st, f32, nrhs);
+}
+
 void launch_nonlocal(const System& s, const QSet& q, const double2* x, double2* out, hipStream_t st, bool f32,
                      int nrhs) {
     if (s.nproj == 0) return;
@@ -571,6 +941,7 @@ void launch_project_signed(const System& s, const QSet& q, double2* phi, double 
                            bool f32, int nrhs) {
     const int nb = s.nbnd, P = q.npw_pad, nbatch = 2 * q.nk;
     const long long bstride = (long long)nb * 2 * P;
+    if (!f32 && !cn_lds_fits(nb, nb) && run_pair(s, q, nullptr, phi, osx, osy, nrhs, st)) return;
     double2* S = s.ws.gsmall;
     run_gemm_cn(s, (const double2* const*)q.d_occ, q.tmod, 2 * P, phi, bstride, 2 * P, nb, nb, 2 * P, nbatch, nrhs,
                 S, st, f32);

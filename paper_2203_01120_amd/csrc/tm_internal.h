@@ -200,6 +200,7 @@ struct QSet {
     double** d_eps = nullptr;
     double2** d_occ = nullptr;
     double2** d_vkb = nullptr;
+    double2** d_gram = nullptr;     // [2 nk] O^dag beta, [(spin, projector)][band]
     int** d_maps = nullptr;       // restriction maps for the start vectors (map_k, map_mk)
     int* d_nrows_kq = nullptr;    // occupied plane rows of each batch's spheres
     int* d_nrows_u = nullptr;
@@ -334,6 +335,9 @@ void launch_ureal(const System& s, const QSet& q, hipStream_t st);
 void launch_fxc_setup(System& s, const double* rho_plane, hipStream_t st);
 void launch_coulomb_setup(const System& s, QSet& q, hipStream_t st);
 // gemm.hip
+void launch_gram(const System& s, const QSet& q, hipStream_t st);
+void launch_nonlocal_project(const System& s, const QSet& q, const double2* x, double2* out, hipStream_t st, bool f32,
+                             int nrhs);
 void launch_nonlocal(const System& s, const QSet& q, const double2* x, double2* out, hipStream_t st,
                      bool f32 = false, int nrhs = 1);
 void launch_project(const System& s, const QSet& q, double2* out, hipStream_t st, bool f32 = false,
