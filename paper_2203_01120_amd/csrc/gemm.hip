@@ -3,7 +3,7 @@
 // Two shapes cover the nonlocal pseudopotential term and the projector onto
 // the empty manifold of every (side, k) block:
 //   k_gemm_cn:     C[m][n] = sum_k conj(A[m][k]) B[n][k]   (small C, long K;
-//                  split over K, partials summed by k_reduce_parts)
+//                  split over K, partials summed by k_reduce_pair)
 //   k_gemm_update: Y[n][k] = os * (Y[n][k] + cs * sum_m C[m][n] A[m][k])
 //                  (long output rows, short inner dimension)
 // Nonlocal term (Eq. H0_k_plus_q, V_NL with the 2x2 spin D matrix):
@@ -273,15 +273,6 @@ __global__ void __launch_bounds__(kCnThreads) k_gemm_cn_lds(GemmCN g, int mt) {
     }
 }
 
-__global__ void k_reduce_parts(const double2* part, double2* out, int ksplit, long long mn, int nbatch) {
-    long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= mn * nbatch) return;
-    long long b = idx / mn, e = idx - b * mn;
-    double2 s = cmk(0.0, 0.0);
-    for (int k = 0; k < ksplit; ++k) s = cadd(s, part[(b * ksplit + k) * mn + e]);
-    out[idx] = s;
-}
-
 struct GemmUpd {
     double2* Y_base;
     long long y_bstride;
@@ -484,7 +475,8 @@ __global__ void __launch_bounds__(64 * kSmallWaves) k_gram(const double2* const*
 }
 
 // Sums of the partials of up to two contractions; 32 elements of 8 slices of the
-// splits a block, added up in slice order.
+// splits a block, added up in slice order.  (A thread an element, as before,
+// waited on one load after the other: 64 x 64 outputs of 512 splits 34 -> 6 us.)
 __global__ void __launch_bounds__(256) k_reduce_pair(const double2* p0, double2* o0, int ks0, long long mn0, const double2* p1,
                                                      double2* o1, int ks1, long long mn1, int blocks0) {
     __shared__ double2 red[8][32];
@@ -759,8 +751,9 @@ void run_gemm_cn(const System& s, const double2* const* A_tab, int amod, int lda
         }
     }
     long long mn = (long long)M * Nn;
-    TM_LAUNCH(k_reduce_parts, dim3((unsigned)((mn * nrhs * nbatch + 255) / 256)), dim3(256), 0, st, s.ws.gpart,
-                       out, g.ksplit, mn, nrhs * nbatch);
+    const int blocks = (int)((mn + 31) / 32);
+    TM_LAUNCH(k_reduce_pair, dim3(blocks, nrhs * nbatch), dim3(256), 0, st, s.ws.gpart, out, g.ksplit, mn, nullptr, nullptr, 0,
+              0, blocks);
 }
 
 // one contraction of the pair: operands and K split (cap: partials of a right-hand side)
@@ -885,7 +878,7 @@ void run_gemm_update(double2* Y, long long y_bstride, int ldy, const double2* C,
     TM_CHECK(ntile <= 16, TM_EUNSUPPORTED, "more than 256 output columns per batch");
     dim3 grid(1, (K + 15) / 16, 2 * nk * nrhs);
     if (f32) {
-        TM_LAUNCH((k_gemm_update<float, 0>), grid, dim3(64 * ntile), 0, st, g);
+        TM_LAUNCH((k_gemm_update<float, 3>), grid, dim3(64 * ntile), 0, st, g);
         return;
     }
     // the variant the autotuner picked for this shape (tuned with one

@@ -691,7 +691,7 @@ struct WTail {
     __device__ static bool live(int lane, int i) { return lane + 64 * i < SLOTS; }
 };
 
-template <int N1, int N2, int BT_, int CPW_, class T2, int NBUF_, int FCH_ = 64, bool FUSE_ = false>
+template <int N1, int N2, int BT_, int CPW_, class T2, int NBUF_>
 struct WaveKernel {
     using G = Geom<N1, N2>;
     // FP64 48 x 48: the lines a wave works on together come in spin pairs (a
@@ -701,10 +701,6 @@ struct WaveKernel {
     // extra cycles per access (measured with a probe).
     static constexpr bool ILV = sizeof(T2) == 16 && N2 == 48;
     using Cols = WCols<N1, N2, CPW_, ILV>;
-    // FUSE: the row fill is fused with the first inverse row stage, and the last
-    // forward row stage with the output (a row's values skip one LDS round trip
-    // at each end)
-    static constexpr bool FUSE = FUSE_;
     static constexpr int NBUF = NBUF_;              // LDS buffers alternating between bands (1 or 2)
     static constexpr int CPW = CPW_;                // columns per wave
     static constexpr int NW = N2 / CPW;             // waves
@@ -777,30 +773,8 @@ struct WaveKernel {
         return wave_rows(2 * nrx, w);
     }
 
-    static constexpr int FIT = cdiv(MAXR * N2, 64);  // row elements per lane, at most
-    static constexpr int FCH = FCH_ < FIT ? FCH_ : FIT;  // of them in flight together
     using Rows = WRows<NW, N2, MAXR, true>;             // line bases in registers (when lane-fixed)
 
-    // row element k = lane + 64 it of the wave: LDS offset within a buffer, and
-    // sphere column (spin plane s, column c; c < 0 outside the sphere)
-    __device__ static bool row_elem(const Smem& m, int nlw, int w, int lane, int it, int& dst, int& s, int& c) {
-        const int k = lane + 64 * it;
-        if (k >= nlw * N2) return false;
-        const int li = k / N2, p2 = k - li * N2;
-        const int l = w + li * NW;
-        const int info = m.rowinfo[l];
-        s = info / N1;
-        const int row = info - s * N1;
-        c = m.colidx[row * N2 + p2];
-        dst = m.rowbase[l] + p2;
-        return true;
-    }
-
-    // fill the wave's occupied rows of buffer boff from the z-transformed
-    // columns of item pair (2n, 2n+1), then the inverse transforms along i2.
-    // FCH > 1: the table reads and column loads of FCH elements are issued
-    // before their LDS stores, so that a lane's elements do not wait on each
-    // other (more registers); FCH = 1: one element at a time.
     // The row fill fused with the first (DIF) stage of the inverse row
     // transform: the lane of butterfly j of row line li loads that row's
     // elements j + t M (t < R) straight from the z-transformed columns (zero
@@ -959,65 +933,14 @@ struct WaveKernel {
         }
     }
 
-    __device__ static void rows_inverse(const Smem& m, const T2* cx, long long cs, int nlw, int w, int boff,
-                                        int lane, const WTw<N2, T2>& gtw2, Rows rl) {
-        if constexpr (FUSE) {
-            rows_inverse_fused(m, cx, cs, nlw, w, boff, lane, gtw2, rl);
-            return;
-        }
-        if constexpr (FCH == 1) {
-            for (int k = lane; k < nlw * N2; k += 64) {
-                const int li = k / N2, p2 = k - li * N2;
-                const int l = w + li * NW;
-                const int info = m.rowinfo[l];
-                const int s = info / N1, row = info - s * N1;
-                const int c = m.colidx[row * N2 + p2];
-                m.pl[boff + m.rowbase[l] + p2] = c >= 0 ? cx[s * cs + c] : Cx<T2>::mk(0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int i0 = 0; i0 < FIT; i0 += FCH) {
-                T2 v[FCH];
-                int dst[FCH];
-#pragma unroll
-                for (int i = 0; i < FCH; ++i) {
-                    int s, c;
-                    v[i] = Cx<T2>::mk(0, 0);
-                    dst[i] = -1;
-                    if (i0 + i < FIT && row_elem(m, nlw, w, lane, i0 + i, dst[i], s, c) && c >= 0)
-                        v[i] = cx[s * cs + c];
-                }
-#pragma unroll
-                for (int i = 0; i < FCH; ++i)
-                    if (dst[i] >= 0) m.pl[boff + dst[i]] = v[i];
-            }
-        }
-        wave_sync();
-        rl.boff = boff;
-        wfft_dif<N2, +1, false, MAXR, BT>(m.pl, rl, nlw, gtw2, lane);
-    }
-
-    // the sphere columns of the wave's rows of buffer boff, to co
-    __device__ static void rows_out(const Smem& m, T2* co, long long cs, int nlw, int w, int boff, int lane) {
-        for (int k = lane; k < nlw * N2; k += 64) {
-            const int li = k / N2, p2 = k - li * N2;
-            const int l = w + li * NW;
-            const int info = m.rowinfo[l];
-            const int s = info / N1, row = info - s * N1;
-            const int c = m.colidx[row * N2 + p2];
-            if (c >= 0) co[s * cs + c] = m.pl[boff + m.rowbase[l] + p2];
-        }
-    }
 };
 
-// MINW: waves per SIMD the register allocation must leave room for; FCH: row
-// elements per lane whose loads are in flight together; EARLY: the band's
-// ground-state loads are issued before its row phase instead of after it
+// MINW: waves per SIMD the register allocation must leave room for; EARLY: the
+// band's ground-state loads are issued before its row phase instead of after it
 // (longer in flight, more registers held through the row stages)
-template <int N1, int N2, int BT, int CPW, class T2, int NBUF, int MINW, int FCH, bool FUSE = false,
-          bool EARLY = false>
+template <int N1, int N2, int BT, int CPW, class T2, int NBUF, int MINW, bool EARLY>
 __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a, PlaneTabs t) {
-    using K = WaveKernel<N1, N2, BT, CPW, T2, NBUF, FCH, FUSE>;
+    using K = WaveKernel<N1, N2, BT, CPW, T2, NBUF>;
     using G = typename K::G;
     using TL = WTail<N1, N2, CPW>;
     constexpr int R = TL::R, IT = TL::IT;
@@ -1072,7 +995,7 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_density_w(PlaneArgs a
                     }
             };
             if constexpr (EARLY) load_u();
-            K::rows_inverse(m, cx, cs, nlw, w, boff, lane, tw2, rl);
+            K::rows_inverse_fused(m, cx, cs, nlw, w, boff, lane, tw2, rl);
             __syncthreads();
             if constexpr (!EARLY) load_u();
             typename K::Cols cl{w * CPW, boff, mask};
@@ -1158,14 +1081,13 @@ __global__ void k_fields_w(const double* __restrict__ vrs, const double2* __rest
 
 // grid: (batch b, chunk, plane i3), so that the blocks in flight share a few
 // planes and their field tables stay in L2
-// AHEAD (with FUSE): 1, the next band's row elements are loaded during this
+// AHEAD: 1, the next band's row elements are loaded during this
 // band's forward row stage, so that its row fill does not wait for them (nor,
 // the memory counter being in order, for this band's output stores); 2, the
 // next band's ground state too, right after this band's products.
-template <int N1, int N2, int BT, int CPW, class T2, int NBUF, int MINW, int FCH, bool FUSE = false,
-          int AHEAD = 0>
+template <int N1, int N2, int BT, int CPW, class T2, int NBUF, int MINW, int AHEAD>
 __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_apply_w(PlaneArgs a, PlaneTabs t) {
-    using K = WaveKernel<N1, N2, BT, CPW, T2, NBUF, FCH, FUSE>;
+    using K = WaveKernel<N1, N2, BT, CPW, T2, NBUF>;
     using G = typename K::G;
     using TL = WTail<N1, N2, CPW>;
     constexpr int PPL = cdiv(K::WPTS, 64);
@@ -1205,7 +1127,6 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_apply_w(PlaneArgs a, 
     const T2* fw = pick<T2>(a.fields, a.fields32) + (long long)(b / a.nb2) * a.fstride +
                    ((long long)i3 * N2 + w * CPW) * 6 * N1;
     const typename K::Rows rl(m.rowbase, w, nlw, lane);
-    static_assert(!AHEAD || FUSE, "row elements loaded ahead need the fused row fill");
     typename K::Fill fill;
     // AHEAD 2: the next band's ground state at the lane's points, loaded ahead
     T2 nu[PPL], nd[PPL];
@@ -1218,15 +1139,13 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_apply_w(PlaneArgs a, 
             nd[j] = Cx<T2>::from(ur[G::NP + q]);
         }
     };
-    if constexpr (AHEAD > 0)
-        if (n0 < n1e)
-            K::fill_load(m, xcols + (((long long)b * a.nitems + 2 * n0) * a.n3 + i3) * a.ncol_max, cs, nlw, w, lane,
-                         fill);
+    if (n0 < n1e)
+        K::fill_load(m, xcols + (((long long)b * a.nitems + 2 * n0) * a.n3 + i3) * a.ncol_max, cs, nlw, w, lane,
+                     fill);
     if constexpr (AHEAD > 1)
         if (n0 < n1e) load_next_u(n0);
     for (int n = n0; n < n1e; ++n) {
         const int boff = NBUF == 2 ? (n & 1) * K::BUF : 0;
-        const T2* cx = xcols + (((long long)b * a.nitems + 2 * n) * a.n3 + i3) * a.ncol_max;
         const double2* ur = ub + ((long long)n * a.n3 + i3) * 2 * G::NP;
         T2 uu[PPL], ud[PPL];
         if constexpr (AHEAD > 1) {
@@ -1245,10 +1164,7 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_apply_w(PlaneArgs a, 
                 }
             }
         }
-        if constexpr (AHEAD > 0)
-            K::fill_finish(m, nlw, boff, lane, tw2, rl, fill);
-        else
-            K::rows_inverse(m, cx, cs, nlw, w, boff, lane, tw2, rl);
+        K::fill_finish(m, nlw, boff, lane, tw2, rl, fill);
         __syncthreads();
         // columns: inverse along i1, point-wise products, forward along i1
         typename K::Cols cl{w * CPW, boff, mask};
@@ -1288,17 +1204,8 @@ __global__ void __launch_bounds__(64 * (N2 / CPW), MINW) k_apply_w(PlaneArgs a, 
         // rows: forward along i2 on the occupied rows of the k+q sphere, then
         // the output columns
         T2* co = xcols + (((long long)b * a.nitems + 2 * n) * a.n3 + i3) * a.ncol_max;
-        if constexpr (AHEAD > 0)
-            if (n + 1 < n1e) K::fill_load(m, co + 2 * a.n3 * a.ncol_max, cs, nlw, w, lane, fill);
-        if constexpr (K::FUSE) {
-            K::rows_forward_out(m, co, cs, nlw, w, boff, lane, tw2, rl);
-        } else {
-            constexpr CPlan c2 = cplan(N2);
-            typename K::Rows rlb = rl;
-            rlb.boff = boff;
-            wfft_dit<N2, -1, K::MAXR, K::BT, c2.nrad - 1>(m.pl, rlb, nlw, tw2, lane);
-            K::rows_out(m, co, cs, nlw, w, boff, lane);
-        }
+        if (n + 1 < n1e) K::fill_load(m, co + 2 * a.n3 * a.ncol_max, cs, nlw, w, lane, fill);
+        K::rows_forward_out(m, co, cs, nlw, w, boff, lane, tw2, rl);
         // no barrier here: with two buffers the next band works in the other
         // one; with one, each wave rewrites only the rows it has just finished
     }
@@ -1336,14 +1243,13 @@ struct WaveVariants {
 template <int N1, int N2, int V>
 void launch_wave_one(bool density, const PlaneArgs& a, const PlaneTabs& t, dim3 wgrid, hipStream_t st) {
     using VV = WaveVariants;
-    constexpr int BT = VV::bt[V], AH = VV::ahead[V], CPW = 4, FCH = 1;
-    constexpr bool FU = true;
-    using K = WaveKernel<N1, N2, BT, CPW, double2, 2, FCH, FU>;
+    constexpr int BT = VV::bt[V], AH = VV::ahead[V], CPW = 4;
+    using K = WaveKernel<N1, N2, BT, CPW, double2, 2>;
     if (density)
-        launch_with_lds(k_density_w<N1, N2, BT, CPW, double2, 2, 1, FCH, FU, true>, "k_density_w", K::bytes(),
+        launch_with_lds(k_density_w<N1, N2, BT, CPW, double2, 2, 1, true>, "k_density_w", K::bytes(),
                         wgrid, K::NT, st, a, t);
     else
-        launch_with_lds(k_apply_w<N1, N2, BT, CPW, double2, 2, 1, FCH, FU, AH>, "k_apply_w", K::bytes(), wgrid,
+        launch_with_lds(k_apply_w<N1, N2, BT, CPW, double2, 2, 1, AH>, "k_apply_w", K::bytes(), wgrid,
                         K::NT, st, a, t);
 }
 
@@ -1363,14 +1269,13 @@ void launch_t(int op, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, hipStre
     // autotuner (3 columns per wave and 16 waves measured slower: idle lanes in
     // the column stages and register spills at 128 VGPRs; one buffer with 6 or 8
     // columns, or 6 waves per SIMD, spill in FP64).  Single precision
-    // (fixed): the apply at 48 x 48 runs 6 columns per wave and 4 waves per
-    // SIMD (2 blocks per CU in 2 x 81 KB of LDS, no spills): 7 % faster; the
-    // density's row fill keeps all of a lane's loads in flight together
-    // (FCH = 64, 10 % faster at 48 x 48); the 6-column apply would spill with it.
-    constexpr int CPW32 = N2 == 20 ? 5 : 4, CPWA32 = N2 == 48 ? 6 : N2 == 20 ? 5 : 4;
-    constexpr int BTD = 2, BTA = N2 == 48 ? 1 : 2;  // 48: two butterflies per load group spill at 128 registers
-    constexpr int NBUF32 = 2, MINW32 = 1, MINWA32 = N2 == 48 ? 4 : 1;
-    constexpr int FCHD32 = 64, FCHA32 = 1;
+    // (fixed): 4 columns per wave, the apply with the next band's row elements
+    // loaded ahead: 48 x 48 x 180, 104 bands, 4 k: 4903 -> 4500 us against 6 columns
+    // per wave, 4 waves per SIMD and separate row stages (with the loads ahead that
+    // shape spills: 6177 us; with the ground state ahead too 4762), 32^3, 32 bands, 9
+    // k: 317 -> 272.  The density fuses the row fill: 2517 -> 2441 and 167 both
+    // (ground state before the row phase: 2574).  All of them give the same bits.
+    constexpr int CPW32 = N2 == 20 ? 5 : 4, BT32 = 2, BTA32 = N2 == 48 ? 1 : 2;
     if (op == kOpUreal) {
         launch_with_lds(k_ureal_t<N1, N2, NT>, "k_ureal_t", PlaneKernel<N1, N2, NT, kU>::bytes(), grid, NT, st, a, t);
     } else if (a.ureal) {
@@ -1384,16 +1289,16 @@ void launch_t(int op, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, hipStre
         const dim3 wgrid(grid.z, (a.nchunk + aw.cpb - 1) / aw.cpb, grid.x);  // (b, chunk group, i3)
         const int nrhs = (int)grid.z / a.nb2;
         if (fp32) {
-            using WD = WaveKernel<N1, N2, BTD, CPW32, float2, NBUF32>;
-            using WA = WaveKernel<N1, N2, BTA, CPWA32, float2, NBUF32>;
+            using WD = WaveKernel<N1, N2, BT32, CPW32, float2, 2>;
+            using WA = WaveKernel<N1, N2, BTA32, CPW32, float2, 2>;
             if (op == kOpDensity) {
-                launch_with_lds(k_density_w<N1, N2, BTD, CPW32, float2, NBUF32, MINW32, FCHD32>, "k_density_w32",
-                                WD::bytes(), wgrid, WD::NT, st, aw, t);
+                launch_with_lds(k_density_w<N1, N2, BT32, CPW32, float2, 2, 1, false>, "k_density_w32", WD::bytes(), wgrid,
+                                WD::NT, st, aw, t);
             } else {
                 TM_LAUNCH((k_fields_w<N1, N2, float2>), dim3((N1 * N2 + 255) / 256, a.n3, nrhs), dim3(256), 0, st,
                           a.vrs, a.W, t.perm2, a.fields32, a.n3, a.wstride, a.fstride);
-                launch_with_lds(k_apply_w<N1, N2, BTA, CPWA32, float2, NBUF32, MINWA32, FCHA32>, "k_apply_w32",
-                                WA::bytes(), wgrid, WA::NT, st, aw, t);
+                launch_with_lds(k_apply_w<N1, N2, BTA32, CPW32, float2, 2, 1, 1>, "k_apply_w32", WA::bytes(), wgrid, WA::NT,
+                                st, aw, t);
             }
             return;
         }
@@ -1748,29 +1653,29 @@ void launch_z(bool inverse, const ZPassArgs& a, int ncolmax, int nbatch, hipStre
             TM_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) == hipSuccess,
                      TM_EDEVICE, "cannot raise the LDS limit of a z pass");
     };
+    auto launch = [&](auto one) {
+        using T2 = decltype(one);
+        if constexpr (PF) {
+            if (inverse) {
+                lds((const void*)k_zinv_p<N3, NT, CT, IT, T2>);
+                TM_LAUNCH((k_zinv_p<N3, NT, CT, IT, T2>), grid, dim3(NT), shm, st, a);
+            } else {
+                lds((const void*)k_zfwd_p<N3, NT, CT, IT, T2>);
+                TM_LAUNCH((k_zfwd_p<N3, NT, CT, IT, T2>), grid, dim3(NT), shm, st, a);
+            }
+        } else if (inverse) {
+            lds((const void*)k_zinv_t<N3, NT, CT, IT, T2>);
+            TM_LAUNCH((k_zinv_t<N3, NT, CT, IT, T2>), grid, dim3(NT), shm, st, a);
+        } else {
+            lds((const void*)k_zfwd_t<N3, NT, CT, IT, T2>);
+            TM_LAUNCH((k_zfwd_t<N3, NT, CT, IT, T2>), grid, dim3(NT), shm, st, a);
+        }
+    };
     if (fp32) {
         TM_CHECK(a.cols32 != nullptr && a.tw32 != nullptr, TM_EINVAL, "missing single-precision buffers");
-        if (inverse) {
-            lds((const void*)k_zinv_t<N3, NT, CT, IT, float2>);
-            TM_LAUNCH((k_zinv_t<N3, NT, CT, IT, float2>), grid, dim3(NT), shm, st, a);
-        } else {
-            lds((const void*)k_zfwd_t<N3, NT, CT, IT, float2>);
-            TM_LAUNCH((k_zfwd_t<N3, NT, CT, IT, float2>), grid, dim3(NT), shm, st, a);
-        }
-    } else if constexpr (PF) {
-        if (inverse) {
-            lds((const void*)k_zinv_p<N3, NT, CT, IT, double2>);
-            TM_LAUNCH((k_zinv_p<N3, NT, CT, IT, double2>), grid, dim3(NT), shm, st, a);
-        } else {
-            lds((const void*)k_zfwd_p<N3, NT, CT, IT, double2>);
-            TM_LAUNCH((k_zfwd_p<N3, NT, CT, IT, double2>), grid, dim3(NT), shm, st, a);
-        }
-    } else if (inverse) {
-        lds((const void*)k_zinv_t<N3, NT, CT, IT, double2>);
-        TM_LAUNCH((k_zinv_t<N3, NT, CT, IT, double2>), grid, dim3(NT), shm, st, a);
+        launch(float2{});
     } else {
-        lds((const void*)k_zfwd_t<N3, NT, CT, IT, double2>);
-        TM_LAUNCH((k_zfwd_t<N3, NT, CT, IT, double2>), grid, dim3(NT), shm, st, a);
+        launch(double2{});
     }
 }
 
@@ -1782,7 +1687,8 @@ bool zpass_fixed_supported(int n3) {
 
 // Launch shapes of the fixed-length z passes (threads NT, columns CT and items
 // IT per block; P: the prefetching kernels) that the autotuner times.
-// Variant 0 is the default, taken untuned and in single precision: a
+// Variant 0 is the default, taken untuned and in single precision (32^3, FP32:
+// the forward pass 53 -> 44 us with the loads up front): a
 // prefetching shape that measured well in both directions for 20, 24, 32, 96
 // and 180.  Every line is transformed alike, so the results are identical.
 // Longer lines: more waves per CU pay (the passes wait on memory, one block
