@@ -70,10 +70,10 @@ __global__ void __launch_bounds__(kZThreads) k_zpass_inv(ZArgs a, FFTPlan pl) {
     lds_fft(lds, L, n3, 1, pl, +1);
     double2* out = a.cols + (long long)b * a.nitems * n3 * a.ncol_stride;
     for (int i = threadIdx.x; i < L * n3; i += blockDim.x) {
-        int cl = i % a.ct;
-        int rest = i / a.ct;
-        int i3 = rest % n3;
-        int il = rest / n3;
+        int rest = index_div(i, a.ct);
+        int cl = i - rest * a.ct;
+        int il = index_div(rest, n3);
+        int i3 = rest - il * n3;
         int c = col0 + cl;
         int item = item0 + il;
         if (c < ncol && item < a.nitems)
@@ -123,10 +123,10 @@ __global__ void __launch_bounds__(kZThreads) k_zpass_fwd(ZFwdArgs a, FFTPlan pl)
     if (col0 >= ncol) return;
     const double2* cin = a.cols + (long long)b * a.nitems * n3 * a.ncol_stride;
     for (int i = threadIdx.x; i < L * n3; i += blockDim.x) {
-        int cl = i % a.ct;
-        int rest = i / a.ct;
-        int i3 = rest % n3;
-        int il = rest / n3;
+        int rest = index_div(i, a.ct);
+        int cl = i - rest * a.ct;
+        int il = index_div(rest, n3);
+        int i3 = rest - il * n3;
         int c = col0 + cl;
         int item = item0 + il;
         double2 v = cmk(0.0, 0.0);
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(kZThreads) k_fft_lines(double2* data, int nlin
     const int l0 = blockIdx.x * lpb;
     // element-major loads: consecutive threads take consecutive lines
     for (int i = threadIdx.x; i < lpb * n; i += blockDim.x) {
-        int ll = i % lpb, t = i / lpb;
+        int t = index_div(i, lpb), ll = i - t * lpb;
         int l = l0 + ll;
         if (l < nlines) {
             long long base = (long long)(l / inner) * outer_stride + (long long)(l % inner) * inner_stride;
@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(kZThreads) k_fft_lines(double2* data, int nlin
     __syncthreads();
     lds_fft(lds, lpb, n, 1, pl, sign);
     for (int i = threadIdx.x; i < lpb * n; i += blockDim.x) {
-        int ll = i % lpb, t = i / lpb;
+        int t = index_div(i, lpb), ll = i - t * lpb;
         int l = l0 + ll;
         if (l < nlines) {
             long long base = (long long)(l / inner) * outer_stride + (long long)(l % inner) * inner_stride;

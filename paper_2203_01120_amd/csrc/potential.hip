@@ -48,6 +48,10 @@ struct PotPlane {
         for (int i = threadIdx.x; i < n2; i += NT) tw2[i] = p2.tw[i];
     }
     __device__ double2& at(int i1, int i2) const { return g[i1 * pitch + i2]; }
+    __device__ double2& flat(int p) const {
+        const int i1 = index_div(p, n2);
+        return at(i1, p - i1 * n2);
+    }
     // after a barrier; ends with one
     __device__ void transform(const FFTPlan& p1, const FFTPlan& p2, int sign) const {
         if constexpr (N > 0) {
@@ -105,21 +109,21 @@ __global__ void __launch_bounds__(plane_threads_ct<N>()) k_rho_planes(const T2* 
         }
         const double2 r = cscale(cmk(sx.x + sgn * sy.x, sx.y + sgn * sy.y), scale);
         if (TURNED) {
-            pl.at(p % n1, p / n1) = r;
+            pl.at(p - index_div(p, n1) * n1, index_div(p, n1)) = r;
         } else {
             rho[p] = r;
-            if (comp == 0) pl.at(p / n2, p % n2) = r;
+            if (comp == 0) pl.flat(p) = r;
         }
     }
     if (!TURNED && comp > 0) return;
     __syncthreads();
     if (TURNED)
-        for (int p = threadIdx.x; p < NP; p += NT) rho[p] = pl.at(p / n2, p % n2);
+        for (int p = threadIdx.x; p < NP; p += NT) rho[p] = pl.flat(p);
     if (comp > 0) return;
     if (TURNED) __syncthreads();
     pl.transform(p1, p2, -1);
     work += rhs * N3 + (long long)i3 * NP;
-    for (int p = threadIdx.x; p < NP; p += NT) work[p] = pl.at(p / n2, p % n2);
+    for (int p = threadIdx.x; p < NP; p += NT) work[p] = pl.flat(p);
 }
 
 // L columns along i3 of right-hand side blockIdx.y: forward, times the Coulomb
@@ -180,7 +184,7 @@ __global__ void __launch_bounds__(plane_threads_ct<N>()) k_pot_planes(const doub
     fxc += off;
     if (first) {
         work += rhs * NN + off;
-        for (int p = threadIdx.x; p < NP; p += NT) pl.at(p / n2, p % n2) = work[p];
+        for (int p = threadIdx.x; p < NP; p += NT) pl.flat(p) = work[p];
         __syncthreads();
         pl.transform(p1, p2, +1);
     }
@@ -229,7 +233,7 @@ __global__ void __launch_bounds__(plane_threads_ct<N>()) k_pot_planes(const doub
             for (int c = 0; c < 4; ++c) r[c] = rho[c * NN + p];
             auto f = [&](int t) { return fxc[t * NN + p]; };
             if (first) {
-                W[p] = cadd(pl.at(p / n2, p % n2), comb(r, f(0), f(1), f(2), f(3)));
+                W[p] = cadd(pl.flat(p), comb(r, f(0), f(1), f(2), f(3)));
             } else {
                 W[NN + p] = comb(r, f(1), f(4), f(5), f(6));
                 W[2 * NN + p] = comb(r, f(2), f(5), f(7), f(8));
