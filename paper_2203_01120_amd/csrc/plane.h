@@ -30,12 +30,11 @@ struct PlaneArgs {
     const double* vrs;
     const double2* W;
     // resident real-space ground state (fixed-size kernels only; null = use
-    // ucols): [slot][nb][n3][2][n1*n2], plane points column-major over the
-    // digit-reversed positions of the in-place transforms, time reversal
-    // applied on the y side
+    // ucols): [slot][nb][n3][spin][p2][i1], p2 the digit-reversed position of
+    // i2, time reversal applied on the y side
     double2* ureal;
     const int* uslot;  // [2nk] slot of each batch
-    double2* fields;   // [n3][n1*n2][6] local fields in the order of the resident planes
+    double2* fields;   // [n3][n1*n2][6] local fields (k_fields_w)
     // single-precision views of xcols, rho_part and fields (FP32 bulk path)
     float2* xcols32;
     float2* rho_part32;
