@@ -161,10 +161,29 @@ inline long long mkey(int a, int b, int c) {
 }
 
 // start vectors: su = sigma^dir (U~_k) on side 0, sigma^dir (T U~_-k) on side 1
-__global__ void k_start(const double2* const* ucoef, const int* npw_u, const int* const* maps, int nk, int nb,
-                        int npw_pad, int dir, double usign_y, double vsign_y, double2* u, double2* v) {
-    const int b = blockIdx.z;
+// (several vectors a launch, e = blockIdx.z / 2 nk: a group of lanes starts from
+// five vectors a lane, which one by one were 120 launches of 24 lanes)
+constexpr int kStartVectors = 32;
+struct StartSet {
+    struct One {
+        const double2* const* ucoef;
+        const int* npw_u;
+        const int* const* maps;
+        double2 *u, *v;
+        int dir;
+        double usign_y, vsign_y;
+    } e[kStartVectors];
+};
+__global__ void k_start(StartSet set, int nk, int nb, int npw_pad) {
+    const StartSet::One& o = set.e[blockIdx.z / (2 * nk)];
+    const int b = blockIdx.z % (2 * nk);
     const int n = blockIdx.y;
+    const double2* const* ucoef = o.ucoef;
+    const int* npw_u = o.npw_u;
+    const int* const* maps = o.maps;
+    const int dir = o.dir;
+    const double usign_y = o.usign_y, vsign_y = o.vsign_y;
+    double2 *u = o.u, *v = o.v;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= npw_pad) return;
     const int side = b >= nk;
@@ -975,15 +994,33 @@ static void apply_l_ready(System& s, QSet& q, const double2* in, double2* out, b
     launch_nonlocal_project(s, q, in, out, st, fp32, nrhs);
 }
 
+// The start vectors of several (q set, direction) at once; v not yet projected.
+struct StartVector {
+    int iq, dir;
+    double2 *u, *v;
+};
+static void start_launch(System& s, const std::vector<StartVector>& all, hipStream_t st) {
+    const QSet& q0 = s.qs[all[0].iq];  // nk and npw_pad are those of every q set
+    for (size_t i0 = 0; i0 < all.size(); i0 += kStartVectors) {
+        StartSet set{};
+        const int cnt = (int)std::min<size_t>(kStartVectors, all.size() - i0);
+        for (int i = 0; i < cnt; ++i) {
+            const StartVector& x = all[i0 + i];
+            const QSet& q = s.qs[x.iq];
+            // lower-side signs: u^l = (s U, t_l s T U), v^m = (P s U, -t_m P+ s T U) with the
+            // time-reversal parity t = -1 of the spin matrices and +1 of sigma_0
+            const double t = x.dir == TM_DIR_N ? 1.0 : -1.0;
+            set.e[i] = {q.d_ucoef, q.d_npw_u, (const int* const*)q.d_maps, x.u, x.v, x.dir, t, -t};
+        }
+        TM_LAUNCH(k_start, dim3((q0.npw_pad + 127) / 128, s.nbnd, 2 * q0.nk * cnt), dim3(128), 0, st, set, q0.nk, s.nbnd,
+                  q0.npw_pad);
+    }
+}
+
 static void start_vectors_raw(System& s, int iq, int dir, double2* u, double2* v, hipStream_t st) {
     QSet& q = s.qs[iq];
     ensure_workspace(s, q);
-    dim3 gr((q.npw_pad + 127) / 128, s.nbnd, 2 * q.nk);
-    // lower-side signs: u^l = (s U, t_l s T U), v^m = (P s U, -t_m P+ s T U) with the
-    // time-reversal parity t = -1 of the spin matrices and +1 of sigma_0
-    const double t = dir == TM_DIR_N ? 1.0 : -1.0;
-    TM_LAUNCH(k_start, gr, dim3(128), 0, st, q.d_ucoef, q.d_npw_u, (const int* const*)q.d_maps, q.nk,
-                       s.nbnd, q.npw_pad, dir, t, -t, u, v);
+    start_launch(s, {{iq, dir, u, v}}, st);
     if (v) launch_project_signed(s, q, v, 1.0, 1.0, st);
 }
 
@@ -1129,20 +1166,24 @@ static void chain_begin(Chain& c, hipStream_t st) {
     TM_HIP(hipMemcpyAsync(c.cs, h.data(), h.size() * sizeof(ChainState), hipMemcpyHostToDevice, st));
     TM_HIP(hipStreamSynchronize(st));  // h is released on return
     const int mdir[kNMeasure] = {TM_DIR_X, TM_DIR_Y, TM_DIR_Z, TM_DIR_N};
-    for (int l = 0; l < kNMeasure; ++l) {
-        if (c.ustride == 0) {
-            start_vectors(s, c.iq, mdir[l], c.u[l], nullptr, st);
-        } else {
-            for (int r = 0; r < c.lanes; ++r)
-                start_vectors(s, c.lane_iq[r], mdir[l], c.u[l] + r * c.ustride, nullptr, st);
-        }
+    // the measure vectors (one set for lanes on one q set) and every lane's start
+    // vector, which is then projected with those of the other lanes
+    std::vector<StartVector> start;
+    for (int l = 0; l < kNMeasure; ++l)
+        for (int r = 0; r < (c.ustride == 0 ? 1 : c.lanes); ++r)
+            start.push_back({c.ustride == 0 ? c.iq : c.lane_iq[r], mdir[l], c.u[l] + r * c.ustride, nullptr});
+    for (int r = 0; r < c.lanes; ++r) {
+        ensure_tuned(s, c.lane_iq[r], st);  // the projection is a tuned contraction
+        start.push_back({c.lane_iq[r], c.dir[r], nullptr, c.V(1) + r * c.n});
     }
+    ensure_workspace(s, *c.qa, c.lanes);
+    start_launch(s, start, st);
+    launch_project_signed(s, *c.qa, c.V(1), 1.0, 1.0, st, false, c.lanes);
     const long long n = c.n, half = c.half, L = c.lanes, us = c.ustride;
     double2* d = c.dots;
     if (c.flavour == TM_PSEUDOHERMITIAN) {
         // roles: 0 q_prev, 1 q, 2 Lq, 3 r, 4 Lr
         TM_HIP(hipMemsetAsync(c.V(0), 0, L * n * sizeof(double2), st));
-        for (int r = 0; r < c.lanes; ++r) start_vectors(s, c.lane_iq[r], c.dir[r], nullptr, c.V(1) + r * n, st);
         apply_l(s, *c.qa, c.V(1), c.V(2), c.fp32, st, c.lanes);
         DotSet<7> ds0{{c.V(1), c.V(1), c.V(2), c.u[0], c.u[1], c.u[2], c.u[3]},
                       {c.V(2), c.V(1), c.V(2), c.V(1), c.V(1), c.V(1), c.V(1)},
@@ -1155,7 +1196,6 @@ static void chain_begin(Chain& c, hipStream_t st) {
         // roles: 0 q_prev, 1 q, 2 p_prev, 3 p, 4 Lq, 5 L^dag p, 6 J p, 7 q^, 8 p^
         TM_HIP(hipMemsetAsync(c.V(0), 0, L * n * sizeof(double2), st));
         TM_HIP(hipMemsetAsync(c.V(2), 0, L * n * sizeof(double2), st));
-        for (int r = 0; r < c.lanes; ++r) start_vectors(s, c.lane_iq[r], c.dir[r], nullptr, c.V(1) + r * n, st);
         TM_HIP(hipMemcpyAsync(c.V(3), c.V(1), L * n * sizeof(double2), hipMemcpyDeviceToDevice, st));
         DotSet<5> ds0{{c.V(1), c.u[0], c.u[1], c.u[2], c.u[3]},
                       {c.V(1), c.V(1), c.V(1), c.V(1), c.V(1)},
