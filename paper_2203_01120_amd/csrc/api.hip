@@ -1001,9 +1001,11 @@ struct StartVector {
 };
 static void start_launch(System& s, const std::vector<StartVector>& all, hipStream_t st) {
     const QSet& q0 = s.qs[all[0].iq];  // nk and npw_pad are those of every q set
-    for (size_t i0 = 0; i0 < all.size(); i0 += kStartVectors) {
+    // as many a launch as its arguments and its grid's third dimension hold
+    const size_t per = std::min<size_t>(kStartVectors, std::max(1, 65535 / (2 * q0.nk)));
+    for (size_t i0 = 0; i0 < all.size(); i0 += per) {
         StartSet set{};
-        const int cnt = (int)std::min<size_t>(kStartVectors, all.size() - i0);
+        const int cnt = (int)std::min(per, all.size() - i0);
         for (int i = 0; i < cnt; ++i) {
             const StartVector& x = all[i0 + i];
             const QSet& q = s.qs[x.iq];
