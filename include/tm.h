@@ -483,7 +483,9 @@ int tm_chi(const tm_coeffs* c, int m_use, const double* omega, int nomega, doubl
  * zero (no overlaps were measured there).  TM_EXTRAP_NONE requires
  * m_total == m_use and equals tm_chi.  m_use >= 4 when extrapolating.
  * Device memory during the call: the inputs and chi (about 104 * m_total +
- * 72 * nomega bytes).  Synchronous.
+ * 76 * nomega bytes), and 64 * m_total + 72 bytes for each frequency that needs
+ * the general elimination (infinite or far from the chain's spectrum, on a pole
+ * of an undamped chain, or with coefficients many orders apart).  Synchronous.
  */
 typedef enum { TM_EXTRAP_NONE = 0, TM_EXTRAP_CONSTANT = 1, TM_EXTRAP_OSC = 2 } tm_extrap;
 int tm_chi_extrapolated(const tm_coeffs* c, int m_use, int m_total, tm_extrap mode, const double* omega,

@@ -16,8 +16,11 @@ namespace tml {
 void launch_kin(const System& s, double* kin, const int* d_mill, int npw, int npw_pad, const double* p, hipStream_t st);
 size_t gemm_partial_elems(int nbatch, int M, int Nn, int K);
 void launch_chi(const double2* alpha, const double* beta, const double2* gamma, const double2* z, int nz, int cap,
-                int M, double n1, const double* omega, int nw, double eta, double2* chi, int* status,
+                int M, double n1, const double* omega, int nw, double eta, double2* chi, int* general,
                 hipStream_t st);
+void launch_chi_pivoted(const double2* alpha, const double* beta, const double2* gamma, const double2* z, int nz,
+                        int cap, int M, double n1, const double* omega, int nw, double eta, double2* work,
+                        double2* chi, int* status, hipStream_t st);
 
 static thread_local std::string g_err;
 void set_error(const std::string& m) { g_err = m; }
@@ -2289,11 +2292,12 @@ static int chi_rows(const tm_coeffs* c, int m_use, int m_total, tm_extrap mode, 
         // host coefficients, extended past M0: alpha, beta, gamma by their mean over
         // the second half of the computed ones (one mean: constant; one per parity
         // of the index: osc), z = 0 beyond M0 (no measured overlaps there).  One
-        // buffer, copied in one piece: alpha, gamma, z rows, beta, omega, and (its
-        // last element, 8 bytes of zero) the status word, ahead of chi on the device
-        const size_t nin = ((size_t)M * (2 + 2 + 2 * nz + 1) + nomega + 1 + 1) / 2 * 2;
+        // buffer, copied in one piece: alpha, gamma, z rows, beta, omega, and (zeros)
+        // the flags of the frequencies, ahead of chi on the device
+        const size_t ncoef = (size_t)M * (2 + 2 + 2 * nz + 1), nflag = ((size_t)nomega + 1) / 2;
+        const size_t nin = (ncoef + nomega + nflag + 1) / 2 * 2;
         const size_t nchi = nz * (size_t)nomega;
-        std::vector<double> hin(nin, 0.0), hout(1 + 2 * nchi);
+        std::vector<double> hin(nin, 0.0);
         double2* ha = reinterpret_cast<double2*>(hin.data());
         double2* hg = ha + M;
         double2* hz = hg + M;
@@ -2331,39 +2335,51 @@ static int chi_rows(const tm_coeffs* c, int m_use, int m_total, tm_extrap mode, 
                 hg[j] = mg[p];
             }
         }
-        // A scaled by a power of two so that its largest entry is about 1 (k_chi
-        // squares its pivots): chi = n1 z A^-1 takes the factor back
-        double big = std::fabs(eta);
-        for (size_t i = 0; i < 4 * (size_t)M; ++i) big = std::max(big, std::fabs(hin[i]));  // alpha, gamma
-        for (int j = 0; j < M; ++j) big = std::max(big, std::fabs(hb[j]));
-        for (int w = 0; w < nomega; ++w) big = std::max(big, std::fabs(hw[w]));
-        int ex = 0;
-        if (std::isfinite(big) && big > 0.0) (void)std::frexp(big, &ex);
-        for (size_t i = 0; i < 4 * (size_t)M; ++i) hin[i] = std::ldexp(hin[i], -ex);
-        for (int j = 0; j < M; ++j) hb[j] = std::ldexp(hb[j], -ex);
-        for (int w = 0; w < nomega; ++w) hw[w] = std::ldexp(hw[w], -ex);
         struct Mem {
             double* p = nullptr;
+            explicit Mem(size_t doubles) {
+                if (hipMalloc((void**)&p, doubles * sizeof(double)) == hipSuccess) return;
+                (void)hipGetLastError();
+                throw Error{TM_ENOMEM, "hipMalloc failed in tm_chi"};
+            }
             ~Mem() { (void)hipFree(p); }
-        } mem;
-        if (hipMalloc((void**)&mem.p, (nin + 2 * nchi) * sizeof(double)) != hipSuccess) {
-            (void)hipGetLastError();
-            mem.p = nullptr;
-            throw Error{TM_ENOMEM, "hipMalloc failed in tm_chi"};
-        }
+        };
+        Mem mem(nin + 2 * nchi);
         double2* da = reinterpret_cast<double2*>(mem.p);
         double2* dg = da + M;
         double2* dz = dg + M;
         double* db = reinterpret_cast<double*>(dz + nz * (size_t)M);
         double* dw = db + M;
-        double* dst = mem.p + nin - 1;
+        const size_t flags = nin - nflag;
         TM_HIP(hipMemcpy(mem.p, hin.data(), nin * sizeof(double), hipMemcpyHostToDevice));
-        launch_chi(da, db, dg, dz, nz, M, M, std::ldexp(c->n1, -ex), dw, nomega, std::ldexp(eta, -ex),
-                   reinterpret_cast<double2*>(mem.p + nin), reinterpret_cast<int*>(dst), nullptr);
-        TM_HIP(hipMemcpy(hout.data(), dst, hout.size() * sizeof(double), hipMemcpyDeviceToHost));
+        launch_chi(da, db, dg, dz, nz, M, M, c->n1, dw, nomega, eta, reinterpret_cast<double2*>(mem.p + nin),
+                   reinterpret_cast<int*>(mem.p + flags), nullptr);
+        std::vector<double> hout(nflag + 2 * nchi);
+        TM_HIP(hipMemcpy(hout.data(), mem.p + flags, hout.size() * sizeof(double), hipMemcpyDeviceToHost));
+        std::copy(hout.begin() + nflag, hout.end(), chi);
+        // the frequencies that k_chi does not answer for
+        const int* general = reinterpret_cast<const int*>(hout.data());
+        std::vector<int> which;
+        for (int w = 0; w < nomega; ++w)
+            if (general[w]) which.push_back(w);
+        if (which.empty()) return TM_OK;
+        const size_t nw = which.size(), nsub = nz * nw;
+        // omega, the status word, chi
+        const size_t head = (nw + 1 + 1) / 2 * 2;
+        std::vector<double> sub(head, 0.0), res(1 + 2 * nsub);
+        for (size_t i = 0; i < nw; ++i) sub[i] = omega[which[i]];
+        Mem rest(head + 2 * nsub + 8 * (size_t)M * nw);
+        TM_HIP(hipMemcpy(rest.p, sub.data(), head * sizeof(double), hipMemcpyHostToDevice));
+        launch_chi_pivoted(da, db, dg, dz, nz, M, M, c->n1, rest.p, (int)nw, eta,
+                           reinterpret_cast<double2*>(rest.p + head + 2 * nsub),
+                           reinterpret_cast<double2*>(rest.p + head), reinterpret_cast<int*>(rest.p + head - 1), nullptr);
+        TM_HIP(hipMemcpy(res.data(), rest.p + head - 1, res.size() * sizeof(double), hipMemcpyDeviceToHost));
         int status = 0;
-        std::memcpy(&status, hout.data(), sizeof(int));
-        std::copy(hout.begin() + 1, hout.end(), chi);
+        std::memcpy(&status, res.data(), sizeof(int));
+        for (int l = 0; l < nz; ++l)
+            for (size_t i = 0; i < nw; ++i)
+                for (int v = 0; v < 2; ++v)
+                    chi[2 * ((size_t)l * nomega + which[i]) + v] = res[1 + 2 * (l * nw + i) + v];
         TM_CHECK(status == 0, TM_EINVAL, "singular tridiagonal system (eta = 0 on a pole?)");
         return TM_OK;
     });
