@@ -803,6 +803,9 @@ bool run_pair(const System& s, const QSet& q, const double2* x, double2* phi, do
               hipStream_t st) {
     const int nb = s.nbnd, P = q.npw_pad, nbatch = 2 * q.nk, all = nbatch * nrhs, np = x ? s.nproj : 0;
     const long long bstride = (long long)nb * 2 * P;
+    // k_update_pair holds 256 bands, but the sequence's update takes both spins of
+    // a band as columns of its own: where one is refused the other is too
+    TM_CHECK((np > 0 ? 2 : 1) * nb <= 256, TM_EUNSUPPORTED, "more than 256 output columns per batch");
     if (coef_lds(np, nb) > 150 * 1024) return false;
     bool sb = false, ss = false;
     const long long mns = (long long)nb * nb, mnb = (long long)np * 2 * nb;
@@ -844,7 +847,6 @@ bool run_pair(const System& s, const QSet& q, const double2* x, double2* phi, do
     TM_LAUNCH(k_coefficients, dim3((nb + kCoefCols - 1) / kCoefCols, all), dim3(kCoefThreads), shm, st, c);
     UpdPair u{phi, c.W, t, q.d_vkb, (const double2* const*)q.d_occ, q.tmod, np, nb, P, q.nk, osx, osy};
     const int ntile = (nb + 15) / 16;
-    TM_CHECK(ntile <= 16, TM_EUNSUPPORTED, "more than 256 output columns per batch");
     const dim3 grid(2, (P + 15) / 16, all);
     if (tune_pick(kTuneUpd, tune_key(nb, nb, nbatch), 3) == 1) {
         TM_LAUNCH(k_update_pair<2>, grid, dim3(64 * ntile), 0, st, u);
