@@ -237,9 +237,9 @@ int tm_liouvillian_apply_multi(tm_system* sys, int iq, int nrhs, const void* xy_
  * method).  Several launches of the apply exist as compiled variants that
  * split the same work differently: the plane density and apply kernels
  * (butterflies per load group, columns per wave, row loads in flight), the z
- * passes (threads, columns and items per block), the projector / P_c
- * contractions (K split) and their updates (loads grouped ahead of the
- * products or not).  Before a system's first tunable launch -- its
+ * passes (threads, columns and items per block), the contractions of the
+ * nonlocal term and the projector (K split) and their updates (loads grouped
+ * ahead of the products or not).  Before a system's first tunable launch -- its
  * first FP64 apply, start vector with a projection (tm_start_vectors with
  * v), FP64 chain begin or restore -- outside a stream capture, every variant
  * is timed on that system's data (the first apply's own vectors, else two
@@ -265,7 +265,9 @@ int tm_liouvillian_apply_multi(tm_system* sys, int iq, int nrhs, const void* xy_
  *     hand-picked default, for shapes not yet tuned).
  *   tm_autotune_force(op, variant): use `variant` of operation op for every
  *     shape (op: 0 plane density, 1 plane apply, 2 z inverse, 3 z forward,
- *     4 contraction, 5 update); -1 returns to the tuned choice.  A variant beyond a
+ *     4 contraction, 5 update of one product: a chain's re-projection of many
+ *     bands, or an apply whose two products do not go together, 6 update of
+ *     both products of an apply); -1 returns to the tuned choice.  A variant beyond a
  *     shape's count makes that apply fail with TM_EINVAL.  For tests.
  *   tm_autotune_report(buf, cap, needed): the tuned shapes as text, one line
  *     each: operation, shape, number of variants, chosen variant, measured

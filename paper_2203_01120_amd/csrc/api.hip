@@ -97,24 +97,34 @@ struct TuneEntry {
 };
 std::mutex g_tune_mu;
 std::map<std::pair<int, long long>, TuneEntry> g_tuned;
-int g_force[kTuneOps] = {-1, -1, -1, -1, -1, -1};
-int g_trial[kTuneOps] = {-1, -1, -1, -1, -1, -1};   // the variant being timed
-long long g_seen_key[kTuneOps];
-int g_seen_n[kTuneOps];
+int g_force[kTuneOps] = {-1, -1, -1, -1, -1, -1, -1};
 bool g_autotune = true;
 const char* const kTuneNames[kTuneOps] = {"plane_density", "plane_apply", "zpass_inverse", "zpass_forward",
-                                           "contraction", "update"};
+                                           "contraction", "update", "update_pair"};
+// what the launches of the thread that tunes ask for, and the variant it times
+struct TunePick {
+    int op;
+    long long key;
+    int nvariants;
+    const char* what;
+};
+struct TuneTrial {
+    int op = -1;
+    long long key = 0;
+    int variant = 0;
+};
+thread_local std::vector<TunePick>* t_picks = nullptr;
+thread_local TuneTrial t_trial;
 }  // namespace
 
-int tune_pick(int op, long long key, int nvariants) {
+int tune_pick(int op, long long key, int nvariants, const char* what) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    g_seen_key[op] = key;
-    g_seen_n[op] = nvariants;
+    if (t_picks) t_picks->push_back({op, key, nvariants, what});
     int v = 0;
     if (g_force[op] >= 0) {
         v = g_force[op];
-    } else if (g_trial[op] >= 0) {
-        v = g_trial[op];
+    } else if (t_trial.op == op && t_trial.key == key) {
+        v = t_trial.variant;
     } else {
         auto it = g_tuned.find({op, key});
         if (it != g_tuned.end()) v = it->second.chosen;
@@ -810,13 +820,15 @@ static void apply_l_ready(System& s, QSet& q, const double2* in, double2* out, b
                           int nrhs);
 
 // ---- the autotuner ---------------------------------------------------------------
-// Times every compiled variant of each tunable launch of one FP64 apply on the
-// system's own data (after a warm-up, at least three runs each and about 2 ms
-// of runs for short launches; HIP events on the apply's stream) and keeps the
-// fastest per shape, once per shape and process:
-// plane density and apply kernels, the two z passes, the projector and P_c
-// contractions.  `out` (one right-hand side) is scratch here; the caller's
-// apply recomputes it with the chosen variants.
+// Times every compiled variant of each tunable launch of one FP64 apply, and of
+// a chain's re-projection, on the system's own data (after a warm-up, at least
+// three runs each and about 2 ms of runs for short launches; HIP events on the
+// apply's stream) and keeps the fastest per shape, once per shape and process:
+// plane apply kernels, the two z passes, the contractions and updates of the
+// nonlocal term and the projector.  A stage is the launches as the apply issues
+// them, and what it asks tune_pick for is what is timed, so that a choice is
+// made on the kernel that it is for.  `out` (one right-hand side) is scratch
+// here; the caller's apply recomputes it with the chosen variants.
 // nrhs > 1 (a chain's first apply with that many lanes): the plane and
 // z-pass launches of that many right-hand sides, whose best shapes differ
 // from one right-hand side's once the grid fills the device; the
@@ -829,80 +841,72 @@ static void autotune(System& s, QSet& q, const double2* in, double2* out, hipStr
     struct Ev {
         hipEvent_t a, b;
         ~Ev() {
+            t_picks = nullptr;
+            t_trial = TuneTrial();
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
         }
     } ev{e0, e1};
     apply_l_ready(s, q, in, out, false, st, nrhs);  // every buffer holds this system's data
     const long long bstride = (long long)s.nbnd * 2 * q.npw_pad;
-    struct Op {
-        int op;
+    struct Stage {
         const char* what;
+        bool lanes;  // timed for every size class of right-hand sides
         std::function<void()> run;
     };
-    const Op ops[] = {
-        {kTuneZInv, "z inverse",
+    const Stage stages[] = {
+        {"z inverse", true,
          [&] { launch_zpass_inv(s, q, false, in, bstride, 2 * s.nbnd, q.npw_pad, s.ws.xcols, st, false, nrhs); }},
-        {kTuneDensity, "density planes", [&] { launch_density(s, q, st, false, nrhs); }},
-        {kTuneApply, "apply planes", [&] { launch_apply_planes(s, q, st, false, nrhs); }},
-        {kTuneZFwd, "z forward", [&] { launch_zpass_fwd(s, q, s.ws.xcols, in, out, st, false, nrhs); }},
-        {kTuneGemm, "P_c contraction", [&] { launch_project(s, q, out, st); }},
-        {kTuneGemm, "projector contraction", [&] { launch_nonlocal(s, q, in, out, st); }},
-        {kTuneUpd, "P_c update", [&] { launch_project(s, q, out, st); }},
-        {kTuneUpd, "projector update", [&] { launch_nonlocal(s, q, in, out, st); }},
+        {"density planes", true, [&] { launch_density(s, q, st, false, nrhs); }},
+        {"apply planes", true, [&] { launch_apply_planes(s, q, st, false, nrhs); }},
+        {"z forward", true, [&] { launch_zpass_fwd(s, q, s.ws.xcols, in, out, st, false, nrhs); }},
+        {"nonlocal term and projector", false, [&] { launch_nonlocal_project(s, q, in, out, st, false, 1); }},
+        {"re-projection", false, [&] { launch_project(s, q, out, st); }},
     };
-    for (const Op& o : ops) {
-        if (nrhs > 1 && (o.op == kTuneGemm || o.op == kTuneUpd)) continue;
-        {
-            std::lock_guard<std::mutex> lock(g_tune_mu);
-            g_seen_n[o.op] = 0;
-        }
-        o.run();  // the default variant; records the launch's shape key and variant count
-        long long key;
-        int n;
-        {
-            std::lock_guard<std::mutex> lock(g_tune_mu);
-            key = g_seen_key[o.op];
-            n = g_seen_n[o.op];
-            if (n <= 1 || g_force[o.op] >= 0 || g_tuned.count({o.op, key})) continue;
-        }
-        std::vector<float> us(n);
-        // runs per variant: at least 3, and for short launches enough for about
-        // 2 ms, so that launch gaps and timer resolution do not decide
-        auto timed = [&](int reps) {
-            TM_HIP(hipEventRecord(e0, st));
-            for (int r = 0; r < reps; ++r) o.run();
-            TM_HIP(hipEventRecord(e1, st));
-            TM_HIP(hipEventSynchronize(e1));
-            float ms = 0;
-            TM_HIP(hipEventElapsedTime(&ms, e0, e1));
-            return ms * 1000.0f / (float)reps;
-        };
-        try {
-            g_trial[o.op] = 0;
+    for (const Stage& o : stages) {
+        if (nrhs > 1 && !o.lanes) continue;
+        std::vector<TunePick> picks;
+        t_picks = &picks;
+        o.run();  // the variants in force
+        t_picks = nullptr;
+        for (const TunePick& p : picks) {
+            {
+                std::lock_guard<std::mutex> lock(g_tune_mu);
+                if (p.nvariants <= 1 || g_force[p.op] >= 0 || g_tuned.count({p.op, p.key})) continue;
+            }
+            // runs per variant: at least 3, and for short launches enough for about
+            // 2 ms, so that launch gaps and timer resolution do not decide
+            auto timed = [&](int reps) {
+                TM_HIP(hipEventRecord(e0, st));
+                for (int r = 0; r < reps; ++r) o.run();
+                TM_HIP(hipEventRecord(e1, st));
+                TM_HIP(hipEventSynchronize(e1));
+                float ms = 0;
+                TM_HIP(hipEventElapsedTime(&ms, e0, e1));
+                return ms * 1000.0f / (float)reps;
+            };
+            std::vector<float> us(p.nvariants);
+            t_trial = {p.op, p.key, 0};
             const float t1 = timed(1);
             const int reps = (int)std::min(200.0f, std::max(3.0f, 2000.0f / std::max(t1, 1.0f)));
-            for (int v = 0; v < n; ++v) {
-                g_trial[o.op] = v;
+            for (int v = 0; v < p.nvariants; ++v) {
+                t_trial.variant = v;
                 o.run();
                 us[v] = timed(reps);
             }
-        } catch (...) {
-            g_trial[o.op] = -1;
-            throw;
+            t_trial = TuneTrial();
+            TuneEntry t;
+            t.op = p.op;
+            t.key = p.key;
+            t.nvariants = p.nvariants;
+            t.chosen = (int)(std::min_element(us.begin(), us.end()) - us.begin());
+            t.us = us;
+            t.shape = std::string(p.what ? p.what : o.what) + " grid " + std::to_string(s.n1) + "x" +
+                      std::to_string(s.n2) + "x" + std::to_string(s.n3) + ", " + std::to_string(s.nbnd) + " bands, " +
+                      std::to_string(q.nk) + " k" + (nrhs > 1 ? ", " + std::to_string(nrhs) + " right-hand sides" : "");
+            std::lock_guard<std::mutex> lock(g_tune_mu);
+            g_tuned[{p.op, p.key}] = t;
         }
-        g_trial[o.op] = -1;
-        TuneEntry t;
-        t.op = o.op;
-        t.key = key;
-        t.nvariants = n;
-        t.chosen = (int)(std::min_element(us.begin(), us.end()) - us.begin());
-        t.us = us;
-        t.shape = std::string(o.what) + " grid " + std::to_string(s.n1) + "x" + std::to_string(s.n2) + "x" +
-                  std::to_string(s.n3) + ", " + std::to_string(s.nbnd) + " bands, " + std::to_string(q.nk) + " k" +
-                  (nrhs > 1 ? ", " + std::to_string(nrhs) + " right-hand sides" : "");
-        std::lock_guard<std::mutex> lock(g_tune_mu);
-        g_tuned[{o.op, key}] = t;
     }
 }
 

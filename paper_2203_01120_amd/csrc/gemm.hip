@@ -685,12 +685,16 @@ int choose_kchunk(int K, long long tiles_times_batch, long long target = 8192) {
     return kc;
 }
 
+// the two products in the autotuner's report
+constexpr const char* kNonlocal = "nonlocal term";
+constexpr const char* kProjector = "projector";
+
 // nbatch batches per right-hand side, nrhs right-hand sides (the K chunking
 // depends on nbatch only, so each right-hand side is summed as when alone);
 // batch b takes A_tab[b % amod]
 void run_gemm_cn(const System& s, const double2* const* A_tab, int amod, int lda, const double2* B_base,
                  long long b_bstride, int ldb, int M, int Nn, int K, int nbatch, int nrhs, double2* out,
-                 hipStream_t st, bool f32 = false) {
+                 hipStream_t st, bool f32, const char* what) {
     GemmCN g;
     g.A_tab = A_tab;
     g.amod = amod;
@@ -722,7 +726,7 @@ void run_gemm_cn(const System& s, const double2* const* A_tab, int amod, int lda
     // system's first apply, and a chain's arithmetic does not depend on which
     // q set happened to be applied first.
     constexpr int kTargets[3] = {1024, 512, 2048};
-    const int tv = f32 ? 0 : tune_pick(kTuneGemm, tune_key(M, Nn, nbatch), 3);
+    const int tv = f32 ? 0 : tune_pick(kTuneGemm, tune_key(M, Nn, nbatch), 3, what);
     if (cn_lds_fits(M, Nn)) {
         g.kchunk = cn_lds_kchunk(K, nbatch, kTargets[tv]);
         g.ksplit = (K + g.kchunk - 1) / g.kchunk;
@@ -758,7 +762,7 @@ void run_gemm_cn(const System& s, const double2* const* A_tab, int amod, int lda
 
 // one contraction of the pair: operands and K split (cap: partials of a right-hand side)
 GemmCN pair_side(const System& s, const double2* const* A_tab, int amod, const double2* B_base, long long b_bstride, int ld,
-                 int M, int Nn, int nbatch, long long cap, bool& staged) {
+                 int M, int Nn, int nbatch, long long cap, const char* what, bool& staged) {
     GemmCN g{};
     g.A_tab = A_tab;
     g.amod = amod;
@@ -771,7 +775,7 @@ GemmCN pair_side(const System& s, const double2* const* A_tab, int amod, const d
     staged = cn_lds_fits(M, Nn);
     if (staged) {
         constexpr int kTargets[3] = {1024, 512, 2048};  // as in run_gemm_cn
-        g.kchunk = cn_lds_kchunk(ld, nbatch, kTargets[tune_pick(kTuneGemm, tune_key(M, Nn, nbatch), 3)]);
+        g.kchunk = cn_lds_kchunk(ld, nbatch, kTargets[tune_pick(kTuneGemm, tune_key(M, Nn, nbatch), 3, what)]);
     } else {
         const int splits = (int)std::max<long long>(1, std::min<long long>(kPairSplits, cap / ((long long)nbatch * M * Nn)));
         g.kchunk = std::max(kPairK, ((ld + splits - 1) / splits + kPairK - 1) / kPairK * kPairK);
@@ -811,9 +815,9 @@ bool run_pair(const System& s, const QSet& q, const double2* x, double2* phi, do
     const long long mns = (long long)nb * nb, mnb = (long long)np * 2 * nb;
     const long long T = nbatch * mns, room = (long long)(s.ws.cap_xcols / s.ws.width) - T - nbatch * mnb;
     GemmCN gs = pair_side(s, (const double2* const*)q.d_occ, q.tmod, phi, bstride, 2 * P, nb, nb, nbatch,
-                          (long long)(s.ws.cap_gpart / s.ws.width), ss);
+                          (long long)(s.ws.cap_gpart / s.ws.width), kProjector, ss);
     GemmCN gb{};
-    if (np > 0) gb = pair_side(s, q.d_vkb, q.tmod, x, bstride, P, np, 2 * nb, nbatch, room, sb);
+    if (np > 0) gb = pair_side(s, q.d_vkb, q.tmod, x, bstride, P, np, 2 * nb, nbatch, room, kNonlocal, sb);
     const long long parts = nbatch * gb.ksplit * mnb;
     if (parts > room) return false;
     // more elements than a block has threads: their sums in a launch of their own
@@ -848,17 +852,17 @@ bool run_pair(const System& s, const QSet& q, const double2* x, double2* phi, do
     UpdPair u{phi, c.W, t, q.d_vkb, (const double2* const*)q.d_occ, q.tmod, np, nb, P, q.nk, osx, osy};
     const int ntile = (nb + 15) / 16;
     const dim3 grid(2, (P + 15) / 16, all);
-    if (tune_pick(kTuneUpd, tune_key(nb, nb, nbatch), 3) == 1) {
-        TM_LAUNCH(k_update_pair<2>, grid, dim3(64 * ntile), 0, st, u);
-    } else {
+    if (tune_pick(kTuneUpdPair, tune_key(nb, np, nbatch), 2) == 0) {
         TM_LAUNCH(k_update_pair<3>, grid, dim3(64 * ntile), 0, st, u);
+    } else {
+        TM_LAUNCH(k_update_pair<2>, grid, dim3(64 * ntile), 0, st, u);
     }
     return true;
 }
 
 void run_gemm_update(double2* Y, long long y_bstride, int ldy, const double2* C, long long c_bstride, int ldc,
                      const double2* const* A_tab, int tmod, int lda, int Nout, int K, int Minner, double cs,
-                     double osx, double osy, int nk, int nrhs, hipStream_t st, bool f32 = false) {
+                     double osx, double osy, int nk, int nrhs, hipStream_t st, bool f32, const char* what) {
     GemmUpd g;
     g.tmod = tmod;
     g.Y_base = Y;
@@ -885,7 +889,7 @@ void run_gemm_update(double2* Y, long long y_bstride, int ldy, const double2* C,
     }
     // the variant the autotuner picked for this shape (tuned with one
     // right-hand side; every variant gives the same result)
-    switch (tune_pick(kTuneUpd, tune_key(Nout, Minner, 2 * nk), 3)) {
+    switch (tune_pick(kTuneUpd, tune_key(Nout, Minner, 2 * nk), 3, what)) {
         case 0: TM_LAUNCH((k_gemm_update<double, 0>), grid, dim3(64 * ntile), 0, st, g); break;
         case 1: TM_LAUNCH((k_gemm_update<double, 2>), grid, dim3(64 * ntile), 0, st, g); break;
         default: TM_LAUNCH((k_gemm_update<double, 3>), grid, dim3(64 * ntile), 0, st, g); break;
@@ -924,12 +928,13 @@ void launch_nonlocal(const System& s, const QSet& q, const double2* x, double2* 
     const long long bstride = (long long)nb * 2 * P;
     double2* Bm = s.ws.gsmall;
     double2* Wm = s.ws.gsmall + (size_t)nrhs * nbatch * s.nproj * 2 * nb;
-    run_gemm_cn(s, q.d_vkb, q.tmod, P, x, bstride, P, s.nproj, 2 * nb, P, nbatch, nrhs, Bm, st, f32);
+    run_gemm_cn(s, q.d_vkb, q.tmod, P, x, bstride, P, s.nproj, 2 * nb, P, nbatch, nrhs, Bm, st, f32,
+                kNonlocal);
     long long tot = (long long)nrhs * nbatch * s.nproj * 2 * nb;
     TM_LAUNCH(k_dmat, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, Bm, s.dvan, Wm, s.nproj, nb,
                        nrhs * nbatch);
     run_gemm_update(out, bstride, P, Wm, (long long)s.nproj * 2 * nb, 2 * nb, q.d_vkb, q.tmod, P, 2 * nb, P,
-                    s.nproj, 1.0, 1.0, 1.0, q.nk, nrhs, st, f32);
+                    s.nproj, 1.0, 1.0, 1.0, q.nk, nrhs, st, f32, kNonlocal);
 }
 
 void launch_project_signed(const System& s, const QSet& q, double2* phi, double osx, double osy, hipStream_t st,
@@ -939,9 +944,9 @@ void launch_project_signed(const System& s, const QSet& q, double2* phi, double 
     if (!f32 && !cn_lds_fits(nb, nb) && run_pair(s, q, nullptr, phi, osx, osy, nrhs, st)) return;
     double2* S = s.ws.gsmall;
     run_gemm_cn(s, (const double2* const*)q.d_occ, q.tmod, 2 * P, phi, bstride, 2 * P, nb, nb, 2 * P, nbatch, nrhs,
-                S, st, f32);
+                S, st, f32, kProjector);
     run_gemm_update(phi, bstride, 2 * P, S, (long long)nb * nb, nb, (const double2* const*)q.d_occ, q.tmod, 2 * P,
-                    nb, 2 * P, nb, -1.0, osx, osy, q.nk, nrhs, st, f32);
+                    nb, 2 * P, nb, -1.0, osx, osy, q.nk, nrhs, st, f32, kProjector);
 }
 
 void launch_project(const System& s, const QSet& q, double2* out, hipStream_t st, bool f32, int nrhs) {

@@ -1,0 +1,59 @@
+"""The autotuner times the launches that applies and chains issue, and no others."""
+import re
+
+import pytest
+
+from gpu_util import say
+from test_gpu_tuning_order import _desc, _tuned
+
+pytestmark = pytest.mark.gpu
+
+PRODUCTS = re.compile(r"k_(gemm|cn_|reduce_pair|dmat|coefficients|update)")
+
+
+def _kernels(tm):
+    """Names of the profiled launches, without template arguments."""
+    return {re.sub(r"<.*", "", name.strip("( ")) for name in tm.tm_profile_read()}
+
+
+@pytest.mark.parametrize("nbnd", [7, 49])
+def test_tuned_products_are_those_that_run(nbnd):
+    """7 bands: one tile, both products in k_cn_pair; 49: the LDS-staged contraction."""
+    import torch
+    import paper_2203_01120_amd as tm
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    tm.load()
+    assert not _tuned(tm, nbnd), "another test already tuned this shape"
+    h = tm.tm_system_create(_desc(tm, nbnd))
+    try:
+        say(f"launches of the tuner, 24^3, {nbnd} bands")
+        n = tm.tm_qset_info_get(h, 0)["nelem"]
+        x = torch.randn(n, dtype=torch.complex128, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+        y = torch.empty_like(x)
+        tm.tm_profile_enable(True)
+        tm.tm_profile_reset()
+        tm.tm_liouvillian_apply(h, 0, x, y)
+        tuning = _kernels(tm)
+        tm.tm_profile_reset()
+        tm.tm_liouvillian_apply(h, 0, x, y)
+        tm.tm_chains_use_graphs(False)
+        tm.tm_lanczos_run(h, 0, "z", "pH", 2)
+        running = _kernels(tm)
+        tm.tm_profile_enable(False)
+        say(f"  tuner {sorted(tuning)}, after it {sorted(running)}")
+        assert any(PRODUCTS.match(k) for k in running)
+        assert {k for k in tuning if PRODUCTS.match(k)} <= running
+        # the merged update has a choice of its own, between kernels with the same result
+        entry = [e for e in _tuned(tm, nbnd) if e["op"] == "update_pair" and e["shape"].startswith("nonlocal")]
+        assert len(entry) == 1 and entry[0]["variants"] == len(entry[0]["us"]) == 2
+        for v in range(2):
+            other = torch.empty_like(y)
+            tm.tm_autotune_force("update_pair", v)
+            tm.tm_liouvillian_apply(h, 0, x, other)
+            torch.cuda.synchronize()
+            assert torch.equal(other, y), v
+    finally:
+        tm.tm_autotune_force("update_pair", -1)
+        tm.tm_chains_use_graphs(True)
+        tm.tm_profile_enable(False)
+        tm.tm_system_destroy(h)
