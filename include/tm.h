@@ -236,11 +236,11 @@ int tm_liouvillian_apply_multi(tm_system* sys, int iq, int nrhs, const void* xy_
  * Autotuning of launch shapes (an implementation device, not part of the
  * method).  Several launches of the apply exist as compiled variants that
  * split the same work differently: the plane density and apply kernels
- * (butterflies per load group, columns per wave, row loads in flight), the z
- * passes (threads, columns and items per block), the contractions of the
- * nonlocal term and the projector (K split) and their updates (loads grouped
- * ahead of the products or not).  Before a system's first tunable launch -- its
- * first FP64 apply, start vector with a projection (tm_start_vectors with
+ * (bands per block group, or butterflies per load group and loads ahead; the
+ * matrix-core density has one variant), the z passes (threads, columns and
+ * items per block), the contractions of the nonlocal term and the projector (K
+ * split) and their updates (loads grouped ahead of the products or not).
+ * Before a system's first tunable launch -- its first FP64 apply, start vector with a projection (tm_start_vectors with
  * v), FP64 chain begin or restore -- outside a stream capture, every variant
  * is timed on that system's data (the first apply's own vectors, else two
  * scratch vectors allocated and freed for the purpose) and the fastest is
@@ -271,8 +271,8 @@ int tm_liouvillian_apply_multi(tm_system* sys, int iq, int nrhs, const void* xy_
  *     shape's count makes that apply fail with TM_EINVAL.  For tests.
  *   tm_autotune_report(buf, cap, needed): the tuned shapes as text, one line
  *     each: operation, shape, number of variants, chosen variant, measured
- *     microseconds per variant (tab-separated).  Writes at most cap bytes
- *     (NUL-terminated) to the caller's buf (may be NULL) and the full size in
+ *     microseconds per variant (tab-separated; none where there is only
+ *     one).  Writes at most cap bytes (NUL-terminated) to the caller's buf (may be NULL) and the full size in
  *     *needed.
  */
 int tm_autotune_enable(int on);

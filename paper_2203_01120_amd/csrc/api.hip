@@ -872,7 +872,19 @@ static void autotune(System& s, QSet& q, const double2* in, double2* out, hipStr
         for (const TunePick& p : picks) {
             {
                 std::lock_guard<std::mutex> lock(g_tune_mu);
-                if (p.nvariants <= 1 || g_force[p.op] >= 0 || g_tuned.count({p.op, p.key})) continue;
+                if (g_force[p.op] >= 0 || g_tuned.count({p.op, p.key})) continue;
+            }
+            TuneEntry t;
+            t.op = p.op;
+            t.key = p.key;
+            t.nvariants = p.nvariants;
+            t.shape = std::string(p.what ? p.what : o.what) + " grid " + std::to_string(s.n1) + "x" +
+                      std::to_string(s.n2) + "x" + std::to_string(s.n3) + ", " + std::to_string(s.nbnd) + " bands, " +
+                      std::to_string(q.nk) + " k" + (nrhs > 1 ? ", " + std::to_string(nrhs) + " right-hand sides" : "");
+            if (p.nvariants <= 1) {  // nothing to choose: listed without a time
+                std::lock_guard<std::mutex> lock(g_tune_mu);
+                g_tuned[{p.op, p.key}] = t;
+                continue;
             }
             // runs per variant: at least 3, and for short launches enough for about
             // 2 ms, so that launch gaps and timer resolution do not decide
@@ -885,25 +897,17 @@ static void autotune(System& s, QSet& q, const double2* in, double2* out, hipStr
                 TM_HIP(hipEventElapsedTime(&ms, e0, e1));
                 return ms * 1000.0f / (float)reps;
             };
-            std::vector<float> us(p.nvariants);
+            t.us.resize(p.nvariants);
             t_trial = {p.op, p.key, 0};
             const float t1 = timed(1);
             const int reps = (int)std::min(200.0f, std::max(3.0f, 2000.0f / std::max(t1, 1.0f)));
             for (int v = 0; v < p.nvariants; ++v) {
                 t_trial.variant = v;
                 o.run();
-                us[v] = timed(reps);
+                t.us[v] = timed(reps);
             }
             t_trial = TuneTrial();
-            TuneEntry t;
-            t.op = p.op;
-            t.key = p.key;
-            t.nvariants = p.nvariants;
-            t.chosen = (int)(std::min_element(us.begin(), us.end()) - us.begin());
-            t.us = us;
-            t.shape = std::string(p.what ? p.what : o.what) + " grid " + std::to_string(s.n1) + "x" +
-                      std::to_string(s.n2) + "x" + std::to_string(s.n3) + ", " + std::to_string(s.nbnd) + " bands, " +
-                      std::to_string(q.nk) + " k" + (nrhs > 1 ? ", " + std::to_string(nrhs) + " right-hand sides" : "");
+            t.chosen = (int)(std::min_element(t.us.begin(), t.us.end()) - t.us.begin());
             std::lock_guard<std::mutex> lock(g_tune_mu);
             g_tuned[{p.op, p.key}] = t;
         }

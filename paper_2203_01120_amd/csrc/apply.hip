@@ -403,10 +403,11 @@ bool mx_path(const System& s, bool fp32) {
     return std::max(s.mmax[0], s.mmax[1]) <= reach;
 }
 
-// bands a group, tuned per shape; the size class of the right-hand sides as for the z passes
+// bands a group of the apply, tuned per shape; the size class of the right-hand
+// sides as for the z passes.  The density has one variant.
 int mx_variant(int op, const System& s, const QSet& q, int nrhs) {
     return tune_pick(op, tune_key(s.n1 * 1000 + s.n2, s.n3 * 2 + (s.ureal_mode == 1), s.nbnd, 2 * q.nk * 64 + rhs_class(nrhs)),
-                     kMxVariants);
+                     op == kTuneDensity ? 1 : kMxVariants);
 }
 
 int plane_threads(const System& s) {

@@ -174,7 +174,7 @@ constexpr int mx_column_reach(int n1) { return n1 == 8 ? 3 : 7 * n1 / 24; }
 // planemx.hip, and the twists exp(-i pi m / n) (1 for odd n)
 std::vector<double2> mx_constants(int n);
 std::vector<double2> mx_twists(int n);
-constexpr int kMxVariants = 3;  // bands in a group: 1, 2, 4 at most
+constexpr int kMxVariants = 3;  // of the apply: bands in a group 1, 2, 4 at most
 // density: returns the partial sums of a batch that it wrote, a.nchunk at most
 int launch_plane_mx(bool density, const MxArgs& a, int nbatch, int variant, hipStream_t st);
 void launch_fields_mx(const double* vrs, const double2* W, void* fields, int n1, int n2, int n3, long long wstride,

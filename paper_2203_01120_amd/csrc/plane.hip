@@ -1229,14 +1229,15 @@ void launch_with_lds(F kernel, const char* name, size_t shm, dim3 grid, int nt, 
 // Variants of the FP64 wave plane kernels (48 x 48) that the autotuner times:
 // BT butterflies per load group, and how far the apply loads ahead (1: the next
 // band's row elements during this band's forward row stage, 2: its ground state
-// too; the density loads a band's ground state before its row phase).  All with
+// too; the density loads a band's ground state before its row phase and has the
+// first two only).  All with
 // 4 columns per wave, two LDS buffers, fused first / last row stages and no
 // occupancy floor.  They split the work differently and do the same arithmetic
 // per point in the same order, so their results are identical.  (Variants with
 // separate row stages are 10 % slower, and the compiler contracts their
 // multiply-adds differently: last bits that depend on the variant.)
 struct WaveVariants {
-    static constexpr int n = 3;
+    static constexpr int n = 3, ndensity = 2;
     static constexpr int bt[n] = {1, 2, 1}, ahead[n] = {1, 1, 2};
 };
 
@@ -1306,9 +1307,9 @@ void launch_t(int op, const PlaneArgs& a, const PlaneTabs& t, dim3 grid, hipStre
         // bands and sides, and the size class of the right-hand side count)
         if constexpr (N1 == 48) {
             const long long key = tune_key(N1 * 1000 + N2, a.n3, a.nb, a.nb2 * 64 + rhs_class(nrhs));
-            constexpr int NV = WaveVariants::n;
+            constexpr int NV = WaveVariants::n, NVD = WaveVariants::ndensity;
             if (op == kOpDensity) {
-                launch_wave_v<N1, N2, NV - 1>(true, tune_pick(kTuneDensity, key, NV), aw, t, wgrid, st, nrhs);
+                launch_wave_v<N1, N2, NVD - 1>(true, tune_pick(kTuneDensity, key, NVD), aw, t, wgrid, st, nrhs);
             } else {
                 TM_CHECK(a.fields != nullptr, TM_EINVAL, "missing field table");
                 TM_LAUNCH((k_fields_w<N1, N2, double2>), dim3((N1 * N2 + 255) / 256, a.n3, nrhs), dim3(256), 0, st,

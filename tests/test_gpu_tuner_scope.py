@@ -57,3 +57,33 @@ def test_tuned_products_are_those_that_run(nbnd):
         tm.tm_chains_use_graphs(True)
         tm.tm_profile_enable(False)
         tm.tm_system_destroy(h)
+
+
+@pytest.mark.parametrize("side,n3,r1,r2,variants", [(20, 6, 5, 4, 1), (24, 6, 9, 8, 1), (45, 5, 6, 7, 1), (48, 6, 18, 16, 2)])
+def test_density_kernels_that_are_one_are_not_timed(side, n3, r1, r2, variants):
+    """One variant on the matrix cores (fixed and other sides), two of the wave kernel."""
+    import torch
+    import paper_2203_01120_amd as tm
+    from test_gpu_planes import _problem
+    from gpu_util import desc_from_problem
+    tm.load()
+    prob = _problem(side, side, n3, r1, r2, 4, 37)
+    h = tm.tm_system_create(desc_from_problem(prob))
+    try:
+        say(f"density variants, {side} x {side} x {n3}")
+        n = tm.tm_qset_info_get(h, 0)["nelem"]
+        x = torch.randn(n, dtype=torch.complex128, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+        y = torch.empty_like(x)
+        tm.tm_liouvillian_apply(h, 0, x, y)
+        entries = [e for e in tm.tm_autotune_report()
+                   if e["op"] == "plane_density" and f"{side}x{side}x{n3}, 4 bands, 1 k" in e["shape"]]
+        say(f"  {entries}")
+        assert len(entries) == 1
+        e = entries[0]
+        assert e["variants"] == variants and len(e["us"]) == (variants if variants > 1 else 0)
+        with pytest.raises(tm.TmError):
+            tm.tm_autotune_force("plane_density", variants)
+            tm.tm_liouvillian_apply(h, 0, x, y)
+    finally:
+        tm.tm_autotune_force("plane_density", -1)
+        tm.tm_system_destroy(h)
