@@ -240,9 +240,9 @@ int tm_liouvillian_apply_multi(tm_system* sys, int iq, int nrhs, const void* xy_
  * matrix-core density has one variant), the z passes (threads, columns and
  * items per block), the contractions of the nonlocal term and the projector (K
  * split) and their updates (loads grouped ahead of the products or not).
- * Before a system's first tunable launch -- its first FP64 apply, start vector with a projection (tm_start_vectors with
- * v), FP64 chain begin or restore -- outside a stream capture, every variant
- * is timed on that system's data (the first apply's own vectors, else two
+ * Before a system's first tunable launch -- its first FP64 apply, start vector
+ * with a projection (tm_start_vectors with v), FP64 chain begin or restore --
+ * outside a stream capture, every variant is timed on that system's data (the first apply's own vectors, else two
  * scratch vectors allocated and freed for the purpose) and the fastest is
  * kept for that shape for the rest of the process; later systems of the same
  * shape reuse it.  So every result of a system comes from the same variants,

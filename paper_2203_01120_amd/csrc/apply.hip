@@ -404,9 +404,11 @@ bool mx_path(const System& s, bool fp32) {
 }
 
 // bands a group of the apply, tuned per shape; the size class of the right-hand
-// sides as for the z passes.  The density has one variant.
+// sides as for the z passes.  The density has one variant.  The reach and the
+// ground state's form decide the kernel (the wave kernels' keys end in 0).
 int mx_variant(int op, const System& s, const QSet& q, int nrhs) {
-    return tune_pick(op, tune_key(s.n1 * 1000 + s.n2, s.n3 * 2 + (s.ureal_mode == 1), s.nbnd, 2 * q.nk * 64 + rhs_class(nrhs)),
+    const int kernel = 2 * (1 + std::max(s.mmax[0], s.mmax[1])) + (s.ureal_mode == 1);
+    return tune_pick(op, tune_key(s.n1 * 1000 + s.n2, s.n3, s.nbnd, 2 * q.nk * 64 + rhs_class(nrhs), kernel),
                      op == kTuneDensity ? 1 : kMxVariants);
 }
 

@@ -80,9 +80,10 @@ inline int rhs_class(int nrhs) {
     }
     return c;
 }
-inline long long tune_key(long long a, long long b = 0, long long c = 0, long long d = 0) {
-    unsigned long long h = 1469598103934665603ULL;  // FNV-1a over the four values
-    for (long long v : {a, b, c, d}) {
+// (e: which of several kernels of one operation the shape takes)
+inline long long tune_key(long long a, long long b = 0, long long c = 0, long long d = 0, long long e = 0) {
+    unsigned long long h = 1469598103934665603ULL;  // FNV-1a over the values
+    for (long long v : {a, b, c, d, e}) {
         h ^= (unsigned long long)v;
         h *= 1099511628211ULL;
     }

@@ -2,8 +2,10 @@
 import re
 
 import pytest
+import torch
 
-from gpu_util import say
+from gpu_util import desc_from_problem, say
+from test_gpu_planes import _problem
 from test_gpu_tuning_order import _desc, _tuned
 
 pytestmark = pytest.mark.gpu
@@ -19,7 +21,6 @@ def _kernels(tm):
 @pytest.mark.parametrize("nbnd", [7, 49])
 def test_tuned_products_are_those_that_run(nbnd):
     """7 bands: one tile, both products in k_cn_pair; 49: the LDS-staged contraction."""
-    import torch
     import paper_2203_01120_amd as tm
     assert torch.cuda.is_available(), "GPU tests need a visible GPU"
     tm.load()
@@ -62,10 +63,7 @@ def test_tuned_products_are_those_that_run(nbnd):
 @pytest.mark.parametrize("side,n3,r1,r2,variants", [(20, 6, 5, 4, 1), (24, 6, 9, 8, 1), (45, 5, 6, 7, 1), (48, 6, 18, 16, 2)])
 def test_density_kernels_that_are_one_are_not_timed(side, n3, r1, r2, variants):
     """One variant on the matrix cores (fixed and other sides), two of the wave kernel."""
-    import torch
     import paper_2203_01120_amd as tm
-    from test_gpu_planes import _problem
-    from gpu_util import desc_from_problem
     tm.load()
     prob = _problem(side, side, n3, r1, r2, 4, 37)
     h = tm.tm_system_create(desc_from_problem(prob))
@@ -87,3 +85,37 @@ def test_density_kernels_that_are_one_are_not_timed(side, n3, r1, r2, variants):
     finally:
         tm.tm_autotune_force("plane_density", -1)
         tm.tm_system_destroy(h)
+
+
+def _tuned_apply_planes(tm, n1, n2, n3, r1, r2, nb, limit):
+    """The plane_apply entries of a shape after a first apply of it."""
+    h = tm.tm_system_create(desc_from_problem(_problem(n1, n2, n3, r1, r2, nb, 41)))
+    try:
+        say(f"plane tuning, {n1} x {n2} x {n3}, reach {r1}, {r2}, resident limit {limit}")
+        tm.tm_system_set_resident_limit(h, limit)
+        n = tm.tm_qset_info_get(h, 0)["nelem"]
+        x = torch.randn(n, dtype=torch.complex128, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+        tm.tm_liouvillian_apply(h, 0, x, torch.empty_like(x))
+        torch.cuda.synchronize()
+        return [e for e in tm.tm_autotune_report()
+                if e["op"] == "plane_apply" and f"{n1}x{n2}x{n3}, {nb} bands, 1 k" in e["shape"]]
+    finally:
+        tm.tm_system_destroy(h)
+
+
+def test_spheres_of_other_kernels_are_tuned_by_themselves():
+    """The reach of the spheres decides which matrix-core kernel runs."""
+    import paper_2203_01120_amd as tm
+    tm.load()
+    assert len(_tuned_apply_planes(tm, 20, 20, 6, 5, 4, 7, -1)) == 1
+    assert len(_tuned_apply_planes(tm, 20, 20, 6, 5, 4, 7, -1)) == 1     # known by now
+    assert len(_tuned_apply_planes(tm, 20, 20, 6, 9, 6, 7, -1)) == 2
+
+
+def test_wave_and_matrix_core_kernels_are_tuned_by_themselves():
+    """48 planes by columns on the matrix cores, and 96 with the resident ground
+    state of full spheres on the wave kernels."""
+    import paper_2203_01120_amd as tm
+    tm.load()
+    assert len(_tuned_apply_planes(tm, 48, 48, 48, 12, 10, 7, 0)) == 1
+    assert len(_tuned_apply_planes(tm, 48, 48, 96, 18, 16, 7, -1)) == 1
