@@ -1741,14 +1741,9 @@ int tm_system_create(const tm_system_desc* d, tm_system** out) {
         for (int iq = 0; iq < d->nq; ++iq) build_qset(s, d, iq, npw_pad, s.qs[iq]);
         s.mx = mx_supported(s.n2, s.n1, s.mmax[1], s.mmax[0]);  // (their axis 1 is i2)
         for (int i = 0; i < 2 && s.mx; ++i) {
-            auto both = [&](const std::vector<double2>& t, double2*& d, float2*& f) {
-                std::vector<float2> h(t.size());
-                for (size_t j = 0; j < t.size(); ++j) h[j] = Cx<float2>::from(t[j]);
-                d = dev_upload(s, t.data(), t.size());
-                f = dev_upload(s, h.data(), h.size());
-            };
-            both(mx_constants(ns[i]), s.ctab[i], s.ctabf[i]);
-            both(mx_twists(ns[i]), s.twist[i], s.twistf[i]);
+            const std::vector<double2> c = mx_constants(ns[i]), t = mx_twists(ns[i]);
+            s.ctab[i] = dev_upload(s, c.data(), c.size());
+            s.twist[i] = dev_upload(s, t.data(), t.size());
         }
         TM_HIP(hipDeviceSynchronize());
         *out = ts.release();
@@ -1914,9 +1909,12 @@ int tm_system_footprint(const tm_system_desc* d, tm_memory_info* out) {
             }
             tables += (double)s.N * sizeof(double);  // Coulomb multiplier
         }
-        // potentials, density and magnetisation, kernel fields; twiddles and permutations
+        // potentials, density and magnetisation, kernel fields; twiddles and
+        // permutations; constants of the matrix-core plane kernels
         tables += (double)s.N * (4 + 4 + 10) * sizeof(double) +
                   (double)(s.n1 + s.n2 + s.n3) * (sizeof(double2) + sizeof(float2) + sizeof(int));
+        for (int n : {s.n1, s.n2})
+            if (n <= kMxSide) tables += (mx_constants(n).size() + mx_twists(n).size()) * sizeof(double2);
         tables = tables * 1.05 + (1 << 20);
         tm_memory_info m{};
         m.tables = (long long)tables;

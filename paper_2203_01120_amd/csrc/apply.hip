@@ -623,7 +623,7 @@ void launch_potential(const System& s, const QSet& q, hipStream_t st, bool fp32,
     if (pot_planes_supported(s)) {
         const bool mx = mx_path(s, fp32);
         const MxArgs m = mx_args(s, q);
-        launch_pot_planes(s, q, mx ? static_cast<double2*>(const_cast<void*>(m.fields)) : nullptr, m.fstride, nrhs, st);
+        launch_pot_planes(s, q, mx ? m.fields : nullptr, m.fstride, nrhs, st);
         return;
     }
     // every radix pass of the in-LDS transform within kMaxBfly butterflies a thread
@@ -658,7 +658,7 @@ void launch_apply_planes(const System& s, const QSet& q, hipStream_t st, bool fp
     if (mx_path(s, fp32)) {
         const MxArgs m = mx_args(s, q);
         if (!pot_planes_supported(s))  // else they are there
-            launch_fields_mx(s.vrs, s.ws.W, const_cast<void*>(m.fields), m.n1, m.n2, m.n3, 4 * s.N, m.fstride, nrhs, st);
+            launch_fields_mx(s.vrs, s.ws.W, m.fields, m.n1, m.n2, m.n3, 4 * s.N, m.fstride, nrhs, st);
         launch_plane_mx(false, m, 2 * q.nk * nrhs, mx_variant(kTuneApply, s, q, nrhs), st);
         return;
     }

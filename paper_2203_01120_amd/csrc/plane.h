@@ -138,16 +138,16 @@ struct MxArgs {
     int cgroups;                 // blocks the columns are split over (density)
     bool dbuf;                   // two row buffers (density)
     long long fstride;           // elements between the field tables of right-hand sides
-    void* xcols;                 // T2 [batch][item][n3][ncol_max]
+    double2* xcols;              // [batch][item][n3][ncol_max]
     const double2* ucols;        // column path: [2 nk][item][n3][ncol_u_max]
     const short* const* colidx_x;  // [n1 n2] column of the k+q sphere at a plane position, or -1
     const short* const* colidx_u;  // the same for the ground-state sphere
-    void* rho_part;              // T2 [batch][chunk][4][N]
-    const void* fields;          // T2, laid out by launch_fields_mx
+    double2* rho_part;           // [batch][chunk][4][N]
+    double2* fields;             // laid out by launch_fields_mx
     const double2* ureal;        // [slot][nb][n3][spin][digit-reversed row][column], or null: column path
     const int* uslot;
-    const void *ctab1, *ctab2;   // T2 mx_constants of both axes
-    const void *twist1, *twist2; // T2 mx_twists of both axes
+    const double2 *ctab1, *ctab2;    // mx_constants of both axes
+    const double2 *twist1, *twist2;  // mx_twists of both axes
 };
 // row buffer: an odd pitch (a column's rows fall into distinct LDS banks), the
 // two spins of a column tile's rows 8 banks of 16 bytes apart
@@ -155,6 +155,7 @@ __host__ __device__ constexpr int mx_pitch(int n2) { return n2 | 1; }
 __host__ __device__ constexpr int mx_spin_stride(int n2, int m1) {
     return ((2 * m1 + 1) * mx_pitch(n2) + 7) / 16 * 16 + 8;
 }
+constexpr int kMxSide = 64;  // longest side of a plane they take
 bool mx_supported(int n1, int n2, int m1, int m2);
 // The reach up to which they take the resident ground state's planes.  At 48 x
 // 48 a sphere that reaches 23 has 6 K steps, twice the products of the
@@ -177,7 +178,7 @@ std::vector<double2> mx_twists(int n);
 constexpr int kMxVariants = 3;  // of the apply: bands in a group 1, 2, 4 at most
 // density: returns the partial sums of a batch that it wrote, a.nchunk at most
 int launch_plane_mx(bool density, const MxArgs& a, int nbatch, int variant, hipStream_t st);
-void launch_fields_mx(const double* vrs, const double2* W, void* fields, int n1, int n2, int n3, long long wstride,
+void launch_fields_mx(const double* vrs, const double2* W, double2* fields, int n1, int n2, int n3, long long wstride,
                       long long fstride, int nrhs, hipStream_t st);
 
 // response density and potential by planes and columns (potential.hip)

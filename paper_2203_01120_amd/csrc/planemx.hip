@@ -212,13 +212,13 @@ struct MxBlock {
         k = lane >> 4;
         n = lane & 15;
         const int e1 = mx_table<KS>(n1);
-        const double2* g1 = static_cast<const double2*>(a.ctab1);
+        const double2* g1 = a.ctab1;
         for (int i = threadIdx.x; i < e1; i += nt) lds[i] = g1[i];
         double2* t2 = lds;
         Y = lds + e1;
         if (!S::fixed && n1 != n2) {
             const int e2 = mx_table<KS>(n2);
-            const double2* g2 = static_cast<const double2*>(a.ctab2);
+            const double2* g2 = a.ctab2;
             t2 = Y;
             for (int i = threadIdx.x; i < e2; i += nt) t2[i] = g2[i];
             Y = t2 + e2;
@@ -269,8 +269,8 @@ struct RowTile {
         const short* ci = (kind == 0 ? a.colidx_x[tb] : a.colidx_u[bt]) + i1;
         const int ncs = kind == 0 ? a.ncol_max : a.ncol_u_max;
         const long long cs = (long long)a.n3 * ncs;
-        src = (kind == 0 ? static_cast<const double2*>(a.xcols) + (long long)b * a.nitems * cs
-                         : reinterpret_cast<const double2*>(a.ucols) + (long long)bt * a.nitems * cs) +
+        src = (kind == 0 ? a.xcols + (long long)b * a.nitems * cs
+                         : a.ucols + (long long)bt * a.nitems * cs) +
               (long long)i3 * ncs + (2 * bl + s) * cs;
 #pragma unroll
         for (int st = 0; st < KS; ++st) {
@@ -280,10 +280,10 @@ struct RowTile {
             const int cm = in && m > 0 ? ci[(n2 - m) * n1] : -1;
             cc[st] = (unsigned)(cp & 0xffff) | ((unsigned)cm << 16);
         }
-        const double2* w1 = static_cast<const double2*>(a.twist1);
+        const double2* w1 = a.twist1;
         ph = w1[q1 < 0 ? -q1 : q1];
         if (q1 < 0) ph.y = -ph.y;
-        tw2 = static_cast<const double2*>(a.twist2) + blk.k;
+        tw2 = a.twist2 + blk.k;
     }
     // twists of columns m2 and -m2 of K step st
     __device__ __forceinline__ void twists(int st, double2& p, double2& m) const {
@@ -366,7 +366,7 @@ struct RowTile {
 // time reversal of the spinor held 8 lanes apart: (up, dn) -> (conj dn, -conj up)
 __device__ __forceinline__ double2 time_reversed(double2 u, int spin) {
     const double x = swap(u.x), y = swap(u.y);
-    return spin == 0 ? Cx<double2>::mk(x, -y) : Cx<double2>::mk(-x, y);
+    return spin == 0 ? cmk(x, -y) : cmk(-x, y);
 }
 
 // phi of the lane's spin at one point: d x + Wd u, plus what the other spin's
@@ -381,7 +381,7 @@ __device__ __forceinline__ double2 local_product(double d, double2 b, double2 wd
     const double cy = fma(wo.y, u.x, fma(wo.x, u.y, fma(by, x.x, b.x * x.y)));
     const double px = fma(-wd.y, u.y, fma(wd.x, u.x, d * x.x));
     const double py = fma(wd.y, u.x, fma(wd.x, u.y, d * x.y));
-    return Cx<double2>::mk(fma(sg, swap(cx), px), fma(sg, swap(cy), py));
+    return cmk(fma(sg, swap(cx), px), fma(sg, swap(cy), py));
 }
 
 // Byte offsets of a lane's points in an array of rows of `stride` bytes: the
@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(64 * NW, MINW) k_density_mx(MxArgs a) {
     const int n0 = ch0 * a.bpc, n1e = min(a.nb, n0 + a.cpb * a.bpc);
     const int half = (RES ? 1 : 2) * 2 * sp;  // elements of one row buffer (one band)
     MxBlock<KS, N, M> k;
-    k.init(a, reinterpret_cast<double2*>(lds_raw), nt);
+    k.init(a, lds_raw, nt);
     __syncthreads();  // the constant tables
     if (w >= a.cwaves) {
         // row wave: tiles w - cwaves, + rwaves, ...
@@ -508,7 +508,7 @@ __global__ void __launch_bounds__(64 * NW, MINW) k_density_mx(MxArgs a) {
     const RowOff uoff(k.k, n1, n1 / 4 * urow, (spin * NP + cc[0]) * (unsigned)sizeof(double2));
     const RowOff uoff1(k.k, n1, n1 / 4 * urow, (spin * NP + cc[1]) * (unsigned)sizeof(double2));
     const long long NN = (long long)NP * a.n3;
-    double2* out = static_cast<double2*>(a.rho_part) + ((long long)b * (TOT ? 1 : a.nchunk) + ch0) * 4 * NN + (long long)i3 * NP;
+    double2* out = a.rho_part + ((long long)b * (TOT ? 1 : a.nchunk) + ch0) * 4 * NN + (long long)i3 * NP;
     const double2* y0 = k.Y + spin * sp + m1 * pitch;
     const double2* inv = k.inv1 + 16 * t;
     auto work = [&](auto kind) {
@@ -642,8 +642,8 @@ __global__ void k_fields_mx(const double* __restrict__ vrs, const double2* __res
     const double2 w0 = W[g], wx = W[N + g], wy = W[2 * N + g], wz = W[3 * N + g];
     const int up = row * 2 * n2 + c, dn = up + n2;  // [row][spin][column]
     double* d = reinterpret_cast<double*>(f);
-    d[up] = (v + bz);
-    d[dn] = (v - bz);
+    d[up] = v + bz;
+    d[dn] = v - bz;
     f[NP + row * n2 + c] = cmk(bx, by);
     f[2 * NP + up] = cadd(w0, wz);
     f[2 * NP + dn] = csub(w0, wz);
@@ -678,7 +678,7 @@ __global__ void __launch_bounds__(64 * NW, MINW) k_apply_mx(MxArgs a) {
     const int ks1 = m1 / 4 + 1;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     MxBlock<KS, N, M> k;
-    k.init(a, reinterpret_cast<double2*>(lds_raw), nt);
+    k.init(a, lds_raw, nt);
     RowTile<KS, RES, N, M> tile[RTW];  // those of w, w + nw, ... the block has
 #pragma unroll
     for (int r = 0; r < RTW; ++r) tile[r].init(a, k, b, bt, tb, i3, w + r * nw);
@@ -691,7 +691,7 @@ __global__ void __launch_bounds__(64 * NW, MINW) k_apply_mx(MxArgs a) {
     if (RES) ub = a.ureal + ((long long)a.uslot[tb] * a.nb * a.n3 + i3) * 2 * NP;
     // field tables of the plane; a lane takes v +- Bz and W0 +- Wz of its spin
     // (the other one's on the y side), and what it adds to the other spin
-    const Buf f(static_cast<const double2*>(a.fields) + (long long)(b / a.nb2) * a.fstride + (long long)i3 * 6 * NP,
+    const Buf f(a.fields + (long long)(b / a.nb2) * a.fstride + (long long)i3 * 6 * NP,
                 6 * NP * sizeof(double2));
     const int sy = spin ^ (yside ? 1 : 0);
     const int n0 = yy * a.bpb, n1e = min(a.nb, n0 + a.bpb);
@@ -821,11 +821,11 @@ int cdiv_i(long long a, long long b) { return (int)((a + b - 1) / b); }
 // LDS of a block: the constants of both axes and `halves` row buffers of bb bands
 // (and room for the forward transforms' reads of whole row tiles of constants)
 template <int KS>
-size_t mx_lds(const MxArgs& a, int halves, size_t esz) {
+size_t mx_lds(const MxArgs& a, int halves) {
     const size_t t1 = mx_table<KS>(a.n1), t = t1 + (a.n1 != a.n2 ? mx_table<KS>(a.n2) : 0);
     constexpr size_t rows = 16 * ((KS + 3) / 4);
     const size_t reach = std::max(rows * mx_stride(a.n1), (t - (a.n1 != a.n2 ? t - t1 : t1)) + rows * mx_stride(a.n2)) + 32;
-    return std::max(t + (size_t)halves * a.bb * 2 * a.sp, reach) * esz;
+    return std::max(t + (size_t)halves * a.bb * 2 * a.sp, reach) * sizeof(double2);
 }
 
 constexpr size_t kMxLds = 160 * 1024;
@@ -872,8 +872,8 @@ int launch_shape(bool density, MxArgs a, int nbatch, int variant, hipStream_t st
         while (colwaves(a.cgroups) + minrow > kDensityW) ++a.cgroups;
         a.cwaves = colwaves(a.cgroups);
         a.rwaves = std::min(a.rtiles, std::max(minrow, cdiv_i(a.cwaves + minrow, 4) * 4 - a.cwaves));
-        a.dbuf = mx_lds<KS>(a, 2 * kinds, sizeof(double2)) <= kMxLds;
-        const size_t shm = mx_lds<KS>(a, (a.dbuf ? 2 : 1) * kinds, sizeof(double2));
+        a.dbuf = mx_lds<KS>(a, 2 * kinds) <= kMxLds;
+        const size_t shm = mx_lds<KS>(a, (a.dbuf ? 2 : 1) * kinds);
         const int nw = a.cwaves + a.rwaves;
         TM_CHECK(shm <= kMxLds && nw <= kDensityW, TM_EUNSUPPORTED, "plane too large for the matrix-core kernels");
         constexpr int NW = N == 48 || N == 0 ? kDensityW : 8, MINW = N == 20 ? 2 : 3;
@@ -915,17 +915,17 @@ int launch_shape(bool density, MxArgs a, int nbatch, int variant, hipStream_t st
         launch_mx(k_density_mx<KS, JT, RES, N, M, NW, MINW, RTW, false>, "k_density_mx", shm, grid, 64 * nw, st, a);
         return chunks;
     } else {
-        // four waves (one a SIMD); FP64 planes of two row tiles with 256 registers,
-        // the others with 168
-        constexpr bool wide = sizeof(double) == 8 && JT == 2 && RES;
+        // four waves (one a SIMD); planes of two row tiles with 256 registers, the
+        // others with 168
+        constexpr bool wide = JT == 2 && RES;
         constexpr int RTW = (RES && JT == 2) || KS > 4 ? 2 : 1, NW = RES ? 4 : kApplyW;
         const int waves = RES ? 4 : 6;
         a.bb = std::max(1, std::min(want, a.nb));
-        while (a.bb > 1 && (rtiles(a.bb) > std::max(RTW * waves, rtiles(1)) || mx_lds<KS>(a, kinds, sizeof(double2)) > kMxLds / 2))
+        while (a.bb > 1 && (rtiles(a.bb) > std::max(RTW * waves, rtiles(1)) || mx_lds<KS>(a, kinds) > kMxLds / 2))
             --a.bb;
         a.rtiles = rtiles(a.bb);
         const int nw = std::min(NW, std::max(cdiv_i(a.rtiles, RTW), std::min(waves, cdiv_i((long long)a.bb * a.n2, 8))));
-        const size_t shm = mx_lds<KS>(a, kinds, sizeof(double2));
+        const size_t shm = mx_lds<KS>(a, kinds);
         TM_CHECK(shm <= kMxLds && a.rtiles <= RTW * nw, TM_EUNSUPPORTED, "plane too large for the matrix-core kernels");
         // bands of a block: whole groups, about 4096 blocks
         const long long per = (long long)nbatch * a.n3;
@@ -985,7 +985,7 @@ int launch_columns(bool density, const MxArgs& a, int nbatch, int variant, hipSt
 // a first K step of rows inside the plane (n >= 4), and one band's row buffers (x
 // and ground state) in LDS
 bool mx_supported(int n1, int n2, int m1, int m2) {
-    if (std::min(n1, n2) < 4 || std::max(n1, n2) > 64 || std::max(m1, m2) > 23) return false;
+    if (std::min(n1, n2) < 4 || std::max(n1, n2) > kMxSide || std::max(m1, m2) > 23) return false;
     const size_t tabs = (size_t)(mx_table<6>(n1) + (n1 != n2 ? mx_table<6>(n2) : 0)) * sizeof(double2);
     return tabs + (size_t)2 * 2 * mx_spin_stride(n2, m1) * sizeof(double2) <= kMxLds;
 }
@@ -1014,10 +1014,10 @@ int launch_plane_mx(bool density, const MxArgs& a, int nbatch, int variant, hipS
     return launch_columns(density, a, nbatch, variant, st);
 }
 
-void launch_fields_mx(const double* vrs, const double2* W, void* fields, int n1, int n2, int n3, long long wstride,
+void launch_fields_mx(const double* vrs, const double2* W, double2* fields, int n1, int n2, int n3, long long wstride,
                       long long fstride, int nrhs, hipStream_t st) {
     const dim3 grid(((n1 + 15) / 16) * ((n2 + 15) / 16), n3, nrhs);
-    TM_LAUNCH(k_fields_mx, grid, dim3(16, 16), 0, st, vrs, W, static_cast<double2*>(fields), n1, n2, n3, wstride, fstride);
+    TM_LAUNCH(k_fields_mx, grid, dim3(16, 16), 0, st, vrs, W, fields, n1, n2, n3, wstride, fstride);
 }
 
 }  // namespace tml

@@ -265,8 +265,6 @@ struct System {
     bool mx = false;                             // the matrix-core plane kernels take this system
     double2* ctab[2] = {nullptr, nullptr};       // their constants for both plane axes
     double2* twist[2] = {nullptr, nullptr};      // and twists
-    float2* ctabf[2] = {nullptr, nullptr};       // the same in single precision
-    float2* twistf[2] = {nullptr, nullptr};
     // ground-state points (device)
     std::vector<double2*> evc;    // [npts] [nb][2][npw]
     std::vector<int> npw;
