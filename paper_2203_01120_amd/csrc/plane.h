@@ -171,6 +171,31 @@ constexpr int mx_resident_reach(int n1) { return n1 == 48 ? 13 : n1 / 2 - 1; }
 // sizes, and there the fullest is still ahead of the generic ones (45 x 40 x 40,
 // reach 19: 1010 against 1536; 60^3, 18: 1054 against 2320).
 constexpr int mx_column_reach(int n1) { return n1 == 8 ? 3 : 7 * n1 / 24; }
+// Rows j of the pairs, their number rounded up to K steps of 4, and the elements
+// between the rows of an axis' constants (odd)
+__host__ __device__ constexpr int mx_pairs(int n) { return (n + 1) / 2; }
+__host__ __device__ constexpr int mx_steps(int n) { return (mx_pairs(n) + 3) / 4; }
+__host__ __device__ constexpr int mx_stride(int n) { return 4 * mx_steps(n) + 1; }
+// partner of row j
+__host__ __device__ constexpr int mx_partner(int n, int j) { return n % 2 == 0 ? n - 1 - j : j == 0 ? 0 : n - j; }
+// the row that the partners of rows j0 + k (j0 a multiple of 4, k = 0 .. 3) are
+// counted from: 3 - k rows on (the first ones of odd n: n - k, row 0 its own)
+__host__ __device__ constexpr int mx_partner_base(int n, int j0) {
+    return n % 2 == 0 ? n - 4 - j0 : j0 == 0 ? 0 : n - 3 - j0;
+}
+// row of the resident ground state that holds row j0 (a multiple of 4) of a plane
+// of n: the digits of j0 / 4 reversed (rows j0 + k are k n / 4 further, every
+// resident size having 4 as its first radix)
+__host__ __device__ constexpr int mx_resident_row(int n, int j0) {
+    const CPlan p = cplan(n);
+    int d = j0 / 4, w = n / 4, r = 0;
+    for (int s = 1; s < p.nrad; ++s) {
+        w /= p.rad[s];
+        r += d % p.rad[s] * w;
+        d /= p.rad[s];
+    }
+    return r;
+}
 // constants of the transforms of length n: rows m = 0 .. 23 of (cos, sin), see
 // planemx.hip, and the twists exp(-i pi m / n) (1 for odd n)
 std::vector<double2> mx_constants(int n);

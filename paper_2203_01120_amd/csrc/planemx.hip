@@ -74,24 +74,18 @@ struct Shape {
     __device__ static int sp(const MxArgs& a) { return fixed ? mx_spin_stride(N, M) : a.sp; }
 };
 
-// Rows j of the pairs, their number rounded up to K steps of 4, and the
-// constants of one axis: (cos, sin) of row m = 0 .. 4 KS - 1 (zero past the
-// last pair) and column j, rows an odd number of elements apart.  Both
+// The constants of one axis: (cos, sin) of row m = 0 .. 4 KS - 1 and column j
+// (zero past the last pair), rows an odd number of elements apart.  Both
 // transforms read their first factor there: the inverse one rows j of column
 // block m (16 neighbours), the forward one rows m at column j (an odd stride),
 // neither with LDS bank conflicts.  (Reads past the table's last rows meet the
 // row buffer behind it and only make results that are not used.)
-__host__ __device__ constexpr int mx_pairs(int n) { return (n + 1) / 2; }
-__host__ __device__ constexpr int mx_steps(int n) { return (mx_pairs(n) + 3) / 4; }
-__host__ __device__ constexpr int mx_stride(int n) { return 4 * mx_steps(n) + 1; }
 template <int KS>
 __host__ __device__ constexpr int mx_table(int n) {
     return 4 * KS * mx_stride(n);
 }
 // planes whose last row tile is at most half full: a density wave takes it for two column tiles
 __host__ __device__ constexpr bool mx_paired(int n) { return n > 32 && mx_pairs(n) % 16 > 0 && mx_pairs(n) % 16 <= 8; }
-// partner of row j
-__host__ __device__ constexpr int mx_partner(int n, int j) { return n % 2 == 0 ? n - 1 - j : j == 0 ? 0 : n - j; }
 
 // Inverse transform of 16 columns: C and S of a row tile.
 template <int KS>
@@ -387,22 +381,6 @@ __device__ __forceinline__ double2 local_product(double d, double2 b, double2 wd
 // Byte offsets of a lane's points in an array of rows of `stride` bytes: the
 // rows j = j0 + k of a K step j0 from the base of row j0, and their partners
 // from the base of mx_partner_base(j0) (both bases wave-uniform).
-__device__ __forceinline__ int mx_partner_base(int n, int j0) {
-    return n % 2 == 0 ? n - 4 - j0 : j0 == 0 ? 0 : n - 3 - j0;
-}
-// row of the resident ground state that holds row j0 (a multiple of 4) of a plane
-// of n: the digits of j0 / 4 reversed (rows j0 + k are k n / 4 further, every
-// resident size having 4 as its first radix)
-__host__ __device__ constexpr int mx_resident_row(int n, int j0) {
-    const CPlan p = cplan(n);
-    int d = j0 / 4, w = n / 4, r = 0;
-    for (int s = 1; s < p.nrad; ++s) {
-        w /= p.rad[s];
-        r += d % p.rad[s] * w;
-        d /= p.rad[s];
-    }
-    return r;
-}
 struct RowOff {
     unsigned p, m, m0;  // m0: the partners of the first step (odd n: row 0 is its own)
     __device__ __forceinline__ RowOff(int k, int n, unsigned stride, unsigned lane_off) {
