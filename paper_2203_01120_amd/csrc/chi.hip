@@ -20,7 +20,8 @@
 // with its rows in global memory and a back substitution; from the bottom 0.95
 // ms with the four rows in one thread, 0.72 with one row a thread, 0.57 with
 // both candidate eliminations formed before the pivot is known, 0.49 with the
-// group reads.
+// group reads, 0.50 with the range of the pivots kept (the call 587 -> 557 us: the
+// host no longer scales the coefficients).
 //
 // k_chi squares its pivots, and the other order of elimination can meet a
 // rounding error where the one from the top meets a zero.  So it answers for

@@ -400,9 +400,11 @@ struct RowOff {
 // flight per column wave.
 //
 // Bounded by the resident ground state's bytes at 48 x 48 (each point of each
-// band is read once: 11.0 GB in 2470 us is 4.5 TB/s, a device copy's rate); the
-// radix kernel took 3028 us, with more of the time in its LDS passes than in
-// the loads.  Small planes: by the latency of a band's chain (row transform,
+// band is read once: 48 x 48 x 180, 104 bands, 4 k 11.0 GB in 2470 us, 4.5 TB/s;
+// 36 k 99.4 GB in 20.7 ms, 4.8, and by the counters 112.8 GB with the columns
+// and partials, 5.4 TB/s, more than a device copy's 4.7, with the matrix cores
+// 45 % busy); the radix kernel took 3028 us at 4 k, with more of the time in its
+// LDS passes than in the loads.  Small planes: by the latency of a band's chain (row transform,
 // barrier, column transform, products).
 //
 // One buffer (two barriers a band) where two do not fit.  TOT: the block has all
@@ -635,10 +637,11 @@ __global__ void k_fields_mx(const double* __restrict__ vrs, const double2* __res
 // forward transforms.
 // RTW: row tiles of a wave, at most
 //
-// Bound: the matrix cores are busy 38 % of the time at 48 x 48 x 180 and the
-// ground state comes in at 2.4 TB/s; what is left is latency inside a wave (a
-// band's row transforms, columns and row transforms are separated by barriers,
-// and the fields of a half step come from L2), with two blocks a CU to hide it.
+// Bound: at 48 x 48 x 180, 104 bands, 36 k (41.1 ms) the counters show the matrix
+// cores busy 38 % of the time and 128 GB moved, 3.1 TB/s, of which the ground
+// state is 99 (2.4 TB/s); what is left is latency inside a wave (a band's row
+// transforms, columns and row transforms are separated by barriers, and the
+// fields of a half step come from L2), with two blocks a CU to hide it.
 // Four-wave blocks with 256 registers a wave (two a SIMD) hold a column tile's
 // ground state in flight; tried and slower at 48 x 48 x 180: fields 4 half
 // steps ahead (spills, 6.1 ms), eight-wave blocks with role-specialised waves
