@@ -775,6 +775,20 @@ struct WaveKernel {
 
     using Rows = WRows<NW, N2, MAXR, true>;             // line bases in registers (when lane-fixed)
 
+    // conj(w) y of the fused row fill.  Single precision spells its operations out:
+    // left to the compiler, the lines of a wave's second pass (a density of more
+    // than 4 rows a wave: 48 x 48, reach 12 and more) were contracted another way
+    // than those of the first, so that a row's last bits depended on the wave and
+    // pass that took it.  This is how the stage rounds in LDS.
+    __device__ static T2 row_twiddle(T2 y, T2 w) {
+        if constexpr (sizeof(T2) == sizeof(float2)) {
+            return Cx<T2>::mk(__builtin_fmaf(y.y, w.y, y.x * w.x), __builtin_fmaf(y.y, w.x, -(y.x * w.y)));
+        } else {
+            w.y = -w.y;
+            return cmul(y, w);
+        }
+    }
+
     // The row fill fused with the first (DIF) stage of the inverse row
     // transform: the lane of butterfly j of row line li loads that row's
     // elements j + t M (t < R) straight from the z-transformed columns (zero
@@ -817,11 +831,7 @@ struct WaveKernel {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     T2 y = u[it][r];
-                    if (r > 0 && jv[it] > 0) {
-                        T2 wv = gtw2.template get<0, N2>(r, jv[it]);
-                        wv.y = -wv.y;
-                        y = cmul(y, wv);
-                    }
+                    if (r > 0 && jv[it] > 0) y = row_twiddle(y, gtw2.template get<0, N2>(r, jv[it]));
                     m.pl[base[it] + r * M] = y;
                 }
             }
@@ -878,11 +888,7 @@ struct WaveKernel {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     T2 y = f.u[it][r];
-                    if (r > 0 && f.jv[it] > 0) {
-                        T2 wv = gtw2.template get<0, N2>(r, f.jv[it]);
-                        wv.y = -wv.y;
-                        y = cmul(y, wv);
-                    }
+                    if (r > 0 && f.jv[it] > 0) y = row_twiddle(y, gtw2.template get<0, N2>(r, f.jv[it]));
                     m.pl[boff + f.base[it] + r * M] = y;
                 }
             }
