@@ -775,13 +775,14 @@ struct WaveKernel {
 
     using Rows = WRows<NW, N2, MAXR, true>;             // line bases in registers (when lane-fixed)
 
-    // conj(w) y of the fused row fill.  Single precision spells its operations out:
-    // left to the compiler, the lines of a wave's second pass (a density of more
-    // than 4 rows a wave: 48 x 48, reach 12 and more) were contracted another way
-    // than those of the first, so that a row's last bits depended on the wave and
-    // pass that took it.  This is how the stage rounds in LDS.
+    // conj(w) y of the fused row fill.  Single precision at 48 spells its operations
+    // out: left to the compiler, the lines of a wave's second pass (a density of
+    // more than 4 rows a wave, reach 12 and more) were contracted another way than
+    // those of the first, so that a row's last bits depended on the wave and pass
+    // that took it.  This is how the stage rounds in LDS; at the other sizes the
+    // compiler contracts both passes alike, as it does in LDS.
     __device__ static T2 row_twiddle(T2 y, T2 w) {
-        if constexpr (sizeof(T2) == sizeof(float2)) {
+        if constexpr (N2 == 48 && sizeof(T2) == sizeof(float2)) {
             return Cx<T2>::mk(__builtin_fmaf(y.y, w.y, y.x * w.x), __builtin_fmaf(y.y, w.x, -(y.x * w.y)));
         } else {
             w.y = -w.y;
