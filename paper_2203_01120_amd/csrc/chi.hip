@@ -25,7 +25,7 @@
 //
 // k_chi squares its pivots, and the other order of elimination can meet a
 // rounding error where the one from the top meets a zero.  So it answers for
-// the frequencies whose pivots lie in 2^+-500 and within a factor 2^40 of each
+// the frequencies whose pivots lie in 2^+-300 and within a factor 2^40 of each
 // other, with finite results; it marks the others (a frequency far from the
 // spectrum or infinite, coefficients far apart, a pole of the undamped chain),
 // and k_chi_pivoted solves those from the top, each with Smith's quotients and
@@ -133,10 +133,11 @@ constexpr int kChiFreqs = kChiThreads / kChiRows; // frequencies of a block
 constexpr int kChiChunk = 64;                     // chain steps staged together
 constexpr int kChiGroup = 4;                      // of them read together
 constexpr int kChiVals = 6;                       // alpha, gamma of the row above, beta, 1 / beta
-// The pivots (|re| + |im|) that k_chi answers for: their squares and reciprocals
-// are normal numbers, and none is so far below the others that it could be a
-// zero but for rounding (a chain of 3000 steps rounds by some 2^-45 of them).
-constexpr double kChiPivotMin = 0x1p-500, kChiPivotMax = 0x1p500, kChiPivotRatio = 0x1p-40;
+// The pivots (|re| + |im|) that k_chi answers for: their squares, reciprocals and
+// products with the couplings are normal numbers, and none is so far below the
+// others that it could be a zero but for rounding (a chain of 3000 steps rounds by
+// some 2^-45 of them).
+constexpr double kChiPivotMin = 0x1p-300, kChiPivotMax = 0x1p300, kChiPivotRatio = 0x1p-40;
 
 __global__ void __launch_bounds__(kChiThreads) k_chi(const double2* __restrict__ alpha,
                                                      const double* __restrict__ beta,
@@ -207,7 +208,7 @@ __global__ void __launch_bounds__(kChiThreads) k_chi(const double2* __restrict__
                 pmin = fmin(pmin, piv);
                 pmax = fmax(pmax, piv);
                 const double s = recip(__builtin_fma(p.x, p.x, p.y * p.y));
-                const double2 fk = cmk(e * (p.x * s), -e * (p.y * s)), fs = cscale(p, ie);
+                const double2 fk = cmk(e * p.x * s, -(e * p.y) * s), fs = cscale(p, ie);
                 const double2 pk = cnma(fk, q, d), ps = cnma(fs, d, q);
                 const double2 zk = cnma(fk, zc, zr), zs = cnma(fs, zr, zc);
                 const double2 qs = cmul(fs, g);
